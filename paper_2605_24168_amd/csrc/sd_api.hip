@@ -785,8 +785,19 @@ sd_status attention_impl(const sd_tensor *q, const sd_kv *K, const sd_kv *V,
   // tens of thousands of candidates in one workgroup per row costs more than
   // selecting full rows over 16 or more workgroups each.
   if (L.dsel_parts >= 16 && cands >= kManyCandidates) w.force_repair = 1;
-  // Those rows select over several workgroups each when they are few.
-  if (w.force_repair && L.dsel_parts) w.dsel_parts = L.dsel_parts;
+  // Those rows select over several workgroups each when they are few and
+  // one workgroup would need several passes over a row (one pass by one
+  // workgroup takes 15-25 us at 32K-128K scores; the pieces' eight kernels
+  // more than that whatever the row).
+  if (w.force_repair && L.dsel_parts) {
+    const sd::RowPlan rp = sd::row_plan((int)std::min<int64_t>(s.ncap, INT32_MAX), sp->n_sink,
+                                        sp->n_local,
+                                        sp->k_override ? k_max
+                                                       : sd::budget_rule(s.ncap, sp->ratio,
+                                                                         sp->k_rounding),
+                                        (int)k_max);
+    if (!sd::row_selects(rp.hi - rp.lo, rp.kh)) w.dsel_parts = L.dsel_parts;
+  }
   sd::Params p = make_params(q, K, V, seq_lens, sp, s, k_max);
   if (labels) {
     p.labels = (const uint16_t *)labels->t.data;

@@ -540,16 +540,6 @@ __device__ __forceinline__ float group_sum(f32x4 acc) {
 // kBlock; the selection also runs 1024-thread blocks when rows are few).
 constexpr int kMaxBlockWaves = 16;
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int wave_incl_scan(int v) {
-  const int l = lane_id();
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(v, o);
-    if (l >= o) v += t;
-  }
-  return v;
-}
-
 // x itself, hidden from the optimiser: values derived from x in one phase
 // are recomputed in the next instead of being kept alive across it.
 __device__ __forceinline__ uint32_t fresh(uint32_t x) {
@@ -563,8 +553,9 @@ __device__ __forceinline__ int lanes_below(uint64_t m) {
 }
 
 // Inclusive prefix sum over the wave's 64 lanes by DPP lane shifts within
-// rows of 16 (1, 2, 4, 8) and the two row broadcasts (no LDS round trips).
-__device__ __forceinline__ int wave_incl_scan_dpp(int v) {
+// rows of 16 (1, 2, 4, 8) and the two row broadcasts (no LDS round trips: a
+// shuffle is one of about 100 cycles, six in a row per reduction).
+__device__ __forceinline__ int wave_incl_scan(int v) {
   v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
   v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
   v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
@@ -574,20 +565,43 @@ __device__ __forceinline__ int wave_incl_scan_dpp(int v) {
   return v;
 }
 
-// f(std::integral_constant<int, u>) for u = 0 .. N-1, unrolled in the
-// source: register arrays indexed by u keep constant indices from the start
-// and stay scalar registers (a loop unrolled later by the compiler can leave
-// them promoted to one vector value that every branch then copies whole).
+// Largest value over the wave's 64 lanes, by the same lane moves (the last
+// lane ends with it).
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  auto step = [&](auto ctrl, auto rows) {
+    const uint32_t t = (uint32_t)__builtin_amdgcn_update_dpp(
+        0, (int)v, decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+    v = t > v ? t : v;
+  };
+  step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});
+  step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});
+  step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});
+  step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});
+  step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});
+  step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// f(std::integral_constant<int, u>) for u = 0 .. min(N, U) - 1 (U the same on
+// every lane), unrolled in the source: register arrays indexed by u keep
+// constant indices from the start and stay scalar registers (a loop unrolled
+// later by the compiler can leave them promoted to one vector value that
+// every branch then copies whole).  The first slot past U leaves the whole
+// run: tests slot by slot would walk through (and fetch, each launch anew)
+// the code of every unused slot; a row of 4 used slots of 40 spent 8 us per
+// pass that way.
 template <int I, int N, class F>
-__device__ __forceinline__ void unroll_for_from(F &f) {
+__device__ __forceinline__ void unroll_slots_from(int U, F &f) {
   if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    unroll_for_from<I + 1, N>(f);
+    if (I < U) {
+      f(std::integral_constant<int, I>{});
+      unroll_slots_from<I + 1, N>(U, f);
+    }
   }
 }
 template <int N, class F>
-__device__ __forceinline__ void unroll_for(F &&f) {
-  unroll_for_from<0, N>(f);
+__device__ __forceinline__ void unroll_slots(int U, F &&f) {
+  unroll_slots_from<0, N>(U, f);
 }
 
 // Exclusive prefix sum over the block in thread order; *total gets the sum.

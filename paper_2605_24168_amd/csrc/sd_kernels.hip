@@ -163,6 +163,30 @@ __global__ __launch_bounds__(kBlock) void k_pilot_score(Params p, Work w) {
 constexpr int kBuckets = 2048;
 constexpr int kPilotMinRank = 48;  // fewest sample ranks above the threshold
 
+// Of the m items in LDS (m <= the threads of the block), the krem-th
+// largest: the thread holding it stores it in sh->digit and the number of
+// items above it in sh->above (equal items agree).  Eight reads in flight:
+// one at a time is an LDS round trip per item (m = 200: 8 us).
+__device__ __forceinline__ void rank_items(const uint32_t *items, int m, int krem, SelShared *sh) {
+  if ((int)threadIdx.x >= m) return;
+  const uint32_t x = items[threadIdx.x];
+  int gt = 0, ge = 0;
+  for (int y0 = 0; y0 < m; y0 += 8) {
+    uint32_t v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = items[y0 + e < m ? y0 + e : m - 1];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      gt += y0 + e < m && v[e] > x ? 1 : 0;
+      ge += y0 + e < m && v[e] >= x ? 1 : 0;
+    }
+  }
+  if (gt < krem && krem <= ge) {
+    sh->digit = x;
+    sh->above = gt;
+  }
+}
+
 template <int NT = kBlock>
 struct BucketShared {
   uint32_t items[NT];  // the k-th bucket's items, at most one per thread
@@ -240,19 +264,7 @@ __device__ bool bucket_kth(const uint32_t *keys, int n, int k, uint32_t kmin, ui
           bs->items[atomicAdd(&bs->n, 1)] = key[u];
     }
     __syncthreads();
-    if (tid < m) {
-      const uint32_t x = bs->items[tid];
-      int gt = 0, ge = 0;
-      for (int y = 0; y < m; ++y) {
-        const uint32_t v = bs->items[y];
-        gt += v > x ? 1 : 0;
-        ge += v >= x ? 1 : 0;
-      }
-      if (gt < krem && krem <= ge) {  // x is the krem-th largest (equal items agree)
-        sh->digit = x;
-        sh->above = gt;
-      }
-    }
+    rank_items(bs->items, m, krem, sh);
     __syncthreads();
     T = sh->digit;
     need_eq = krem - sh->above;
@@ -266,12 +278,8 @@ __device__ bool bucket_kth(const uint32_t *keys, int n, int k, uint32_t kmin, ui
 // Ends with a barrier (so LDS written before the call is visible after it).
 template <int NT = kBlock>
 __device__ __forceinline__ void block_key_range(uint32_t &mn, uint32_t &mx, uint32_t (*tmp)[2]) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const uint32_t a = __shfl_xor(mn, o), c = __shfl_xor(mx, o);
-    mn = a < mn ? a : mn;
-    mx = c > mx ? c : mx;
-  }
+  mn = ~wave_max_u32(~mn);
+  mx = wave_max_u32(mx);
   if (lane_id() == 0) {
     tmp[wave_id()][0] = mn;
     tmp[wave_id()][1] = mx;
@@ -1133,6 +1141,7 @@ __global__ __launch_bounds__(kBlock) void k_repair_score(Params p, Work w) {
 //           k_repair_score) is selected from its full scores in w.dense, any
 //           other row from its candidates.
 //   MODE 1: over a full score row (sparse_decode_topk).
+//   MODE 2: the fused path when every row is selected from its full scores.
 // Output: idx[row][0..k) ascending positions, then -1; vals[row][...] the
 // kept scores (or -inf), when vals is not null.
 // ---------------------------------------------------------------------------
@@ -1306,7 +1315,7 @@ __device__ __forceinline__ void find_rank_bin(const uint32_t *hist, int nb, int 
   int mine = 0;
   for (int j = 1; j <= bpt; ++j) mine += (int)hist[hi - j];
   // Exclusive scan of the bin sums over the block.
-  const int inc = wave_incl_scan_dpp(mine);
+  const int inc = wave_incl_scan(mine);
   if (lane_id() == 63) sh->scan[wave_id()] = inc;
   __syncthreads();
   int before = inc - mine;
@@ -1372,10 +1381,13 @@ struct RegShare {
 template <int NT>
 __device__ __forceinline__ RegShare reg_share(int ia, int ib) {
   constexpr int NW = NT / 64;
-  const int n = ib - ia, per = (n + NW - 1) / NW;
+  const int n = __builtin_amdgcn_readfirstlane(ib - ia), per = (n + NW - 1) / NW;
   RegShare s;
-  s.i0 = ia + min(n, wave_id() * per);
-  s.i1 = ia + min(n, wave_id() * per + per);
+  // (Scalar registers: bounds the compiler takes for lane-dependent make
+  // every slot's test an exec mask, kept alive over all the passes.)
+  const int wv = __builtin_amdgcn_readfirstlane(wave_id());
+  s.i0 = ia + min(n, wv * per);
+  s.i1 = ia + min(n, wv * per + per);
   s.U = (s.i1 - s.i0 + 63) >> 6;
   return s;
 }
@@ -1404,35 +1416,29 @@ __device__ __forceinline__ uint32_t reg_load(const ChunkCands &src, const RegSha
   const auto gkey = uniform_ptr(src.gkey);
   const auto gpos = uniform_ptr(src.gpos);
   uint32_t gp[UMAX];
-  unroll_for<UMAX>([&](auto uc) {
+  unroll_slots<UMAX>(U, [&](auto uc) {
     constexpr int u = decltype(uc)::value;
-    key[u] = 0u;
-    gp[u] = 0u;
-    if (u < U) {  // wave-uniform
-      const int ie = min(i0 + 64 * u + lane, i1 - 1);
-      const int cu = __builtin_amdgcn_readlane(cs, u), cn = __builtin_amdgcn_readlane(cs, u + 1);
-      int c = cu, d = __builtin_amdgcn_readlane(ds, u);
-      if (cn != cu) {  // the slot crosses chunk boundaries: count those at or below ie
-        for (int x = cu + 1; x <= cn; ++x) c += src.pre[x] <= ie ? 1 : 0;
-        d = c * src.cap + src.start[c] - src.pre[c];
-      }
-      const uint32_t e = (uint32_t)(d + ie);
-      key[u] = gkey[e];
-      gp[u] = gpos[e];
-      pos_l[ie - ia] = (uint32_t)c * (uint32_t)src.ck;
+    const int ie = min(i0 + 64 * u + lane, i1 - 1);
+    const int cu = __builtin_amdgcn_readlane(cs, u), cn = __builtin_amdgcn_readlane(cs, u + 1);
+    int c = cu, d = __builtin_amdgcn_readlane(ds, u);
+    if (cn != cu) {  // the slot crosses chunk boundaries: count those at or below ie
+      for (int x = cu + 1; x <= cn; ++x) c += src.pre[x] <= ie ? 1 : 0;
+      d = c * src.cap + src.start[c] - src.pre[c];
     }
+    const uint32_t e = (uint32_t)(d + ie);
+    key[u] = gkey[e];
+    gp[u] = gpos[e];
+    pos_l[ie - ia] = (uint32_t)c * (uint32_t)src.ck;
   });
   uint32_t mx = 0u;
-  unroll_for<UMAX>([&](auto uc) {
+  unroll_slots<UMAX>(U, [&](auto uc) {
     constexpr int u = decltype(uc)::value;
-    if (u < U) {
-      const int i = i0 + 64 * u + lane;
-      const bool valid = i < i1;
-      const uint32_t x = fresh(key[u]);
-      atomicAdd(valid ? &pos_l[i - ia] : &sink[lane], gp[u]);
-      on_key(x, valid);
-      mx = valid && x > mx ? x : mx;
-    }
+    const int i = i0 + 64 * u + lane;
+    const bool valid = i < i1;
+    const uint32_t x = fresh(key[u]);
+    atomicAdd(valid ? &pos_l[i - ia] : &sink[lane], gp[u]);
+    on_key(x, valid);
+    mx = valid && x > mx ? x : mx;
   });
   return mx;
 }
@@ -1444,39 +1450,39 @@ __device__ __forceinline__ uint32_t reg_load(const ChunkCands &src, const RegSha
 // softmax weights against vmax.  Entries at or past k are not written.
 // ties: whether the wave holds a key equal to T (else a key is kept iff it
 // is above T, and the tie count is skipped).
-template <int UMAX>
-__device__ __forceinline__ void reg_emit(const uint32_t (&key)[UMAX], const RegShare &sh, int ia,
+// pos(i): the position of item i.  CHECK: a share's end is checked (false:
+// lanes without an item hold key 0, which is never kept).
+template <int UMAX, class PosOf, bool CHECK = true>
+__device__ __forceinline__ void reg_emit(const uint32_t (&key)[UMAX], const RegShare &sh,
                                          uint32_t T, int need_eq, int eq_b, int sel0, int k,
-                                         bool ties, const uint32_t *pos_l, int32_t *irow,
-                                         float *vrow, bool weights, float vmax, float c2) {
+                                         bool ties, PosOf pos, int32_t *irow, float *vrow,
+                                         bool weights, float vmax, float c2) {
   const int lane = lane_id();
   const auto lst = uniform_ptr(irow);
   const auto val = uniform_ptr(vrow);
   auto emit = [&](auto vals, auto wts, auto tie) {
     int eq_run = eq_b, sel_run = sel0;
-    unroll_for<UMAX>([&](auto uc) {
+    unroll_slots<UMAX>(sh.U, [&](auto uc) {
       constexpr int u = decltype(uc)::value;
-      if (u < sh.U) {
-        const int i = sh.i0 + 64 * u + lane;
-        const bool valid = i < sh.i1;
-        const uint32_t x = fresh(key[u]);
-        bool kept = valid && x > T;
-        if constexpr (decltype(tie)::value) {
-          const uint64_t eqm = __ballot(valid && x == T);
-          kept = kept || (valid && x == T && eq_run + lanes_below(eqm) < need_eq);
-          eq_run += __popcll(eqm);
-        }
-        const uint64_t km = __ballot(kept);
-        const int s = sel_run + lanes_below(km);
-        if (kept && s < k) {
-          lst[s] = (int32_t)pos_l[i - ia];
-          if constexpr (decltype(vals)::value) {
-            const float v = key2f(x);
-            val[s] = decltype(wts)::value ? kept_weight(v, vmax, c2) : v;
-          }
-        }
-        sel_run += __popcll(km);
+      const int i = sh.i0 + 64 * u + lane;
+      const bool valid = !CHECK || i < sh.i1;
+      const uint32_t x = fresh(key[u]);
+      bool kept = valid && x > T;
+      if constexpr (decltype(tie)::value) {
+        const uint64_t eqm = __ballot(valid && x == T);
+        kept = kept || (valid && x == T && eq_run + lanes_below(eqm) < need_eq);
+        eq_run += __popcll(eqm);
       }
+      const uint64_t km = __ballot(kept);
+      const int s = sel_run + lanes_below(km);
+      if (kept && s < k) {
+        lst[s] = (int32_t)pos(i);
+        if constexpr (decltype(vals)::value) {
+          const float v = key2f(x);
+          val[s] = decltype(wts)::value ? kept_weight(v, vmax, c2) : v;
+        }
+      }
+      sel_run += __popcll(km);
     });
   };
   auto emit_ties = [&](auto vals, auto wts) {
@@ -1520,11 +1526,7 @@ __device__ __forceinline__ void select_regs(const ChunkCands &src, int n, int k,
   uint32_t mx = reg_load<UMAX>(src, shr, 0, key, pos_l, rs->sink, [&](uint32_t x, bool valid) {
     atomicAdd(valid ? &hist[kb.of(x)] : &rs->sink[lane_id()], 1u);
   });
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const uint32_t t = (uint32_t)__shfl_xor((int)mx, o);
-    mx = t > mx ? t : mx;
-  }
+  mx = wave_max_u32(mx);
   if (lane == 0) rs->wmax[wv] = mx;
   __syncthreads();
   // 3. The k-th largest key T; need_eq of the keys equal to T are kept.
@@ -1539,35 +1541,21 @@ __device__ __forceinline__ void select_regs(const ChunkCands &src, int n, int k,
   if (m <= NT) {
     // Keys above the k-th bucket per wave; the bucket's keys (and waves).
     int gt_w = 0;
-    unroll_for<UMAX>([&](auto uc) {
+    unroll_slots<UMAX>(U, [&](auto uc) {
       constexpr int u = decltype(uc)::value;
-      if (u < U) {
-        const bool valid = i0 + 64 * u + lane < i1;
-        const uint32_t x = fresh(key[u]);
-        const int bk = kb.of(x);
-        gt_w += __popcll(__ballot(valid && bk > bstar));
-        if (valid && bk == bstar) {
-          const int j = atomicAdd(&bs->n, 1);
-          bs->items[j] = x;
-          rs->wave[j] = (uint8_t)wv;
-        }
+      const bool valid = i0 + 64 * u + lane < i1;
+      const uint32_t x = fresh(key[u]);
+      const int bk = kb.of(x);
+      gt_w += __popcll(__ballot(valid && bk > bstar));
+      if (valid && bk == bstar) {
+        const int j = atomicAdd(&bs->n, 1);
+        bs->items[j] = x;
+        rs->wave[j] = (uint8_t)wv;
       }
     });
     if (lane == 0) rs->gt[wv] = (uint32_t)gt_w;
     __syncthreads();
-    if ((int)threadIdx.x < m) {
-      const uint32_t x = bs->items[threadIdx.x];
-      int gt = 0, ge = 0;
-      for (int y = 0; y < m; ++y) {
-        const uint32_t v = bs->items[y];
-        gt += v > x ? 1 : 0;
-        ge += v >= x ? 1 : 0;
-      }
-      if (gt < krem && krem <= ge) {  // x is the krem-th largest (equal keys agree)
-        sh->digit = x;
-        sh->above = gt;
-      }
-    }
+    rank_items(bs->items, m, krem, sh);
     __syncthreads();
     T = sh->digit;
     need_eq = krem - (int)sh->above;
@@ -1593,12 +1581,10 @@ __device__ __forceinline__ void select_regs(const ChunkCands &src, int n, int k,
       __syncthreads();  // the previous readers of hist and sh are done
       for (int j = threadIdx.x; j < nb; j += NT) hist[j] = 0;
       __syncthreads();
-      unroll_for<UMAX>([&](auto uc) {
+      unroll_slots<UMAX>(U, [&](auto uc) {
         constexpr int u = decltype(uc)::value;
-        if (u < U) {
-          const uint32_t x = fresh(key[u]);
-          hist_add(hist, (x >> sft) & dmask, i0 + 64 * u + lane < i1 && (x & mask) == prefix);
-        }
+        const uint32_t x = fresh(key[u]);
+        hist_add(hist, (x >> sft) & dmask, i0 + 64 * u + lane < i1 && (x & mask) == prefix);
       });
       __syncthreads();
       find_rank_bin<NT>(hist, nb, kr, sh);
@@ -1609,14 +1595,12 @@ __device__ __forceinline__ void select_regs(const ChunkCands &src, int n, int k,
     T = prefix;
     need_eq = kr;
     int gt_w = 0, eq_w = 0;
-    unroll_for<UMAX>([&](auto uc) {
+    unroll_slots<UMAX>(U, [&](auto uc) {
       constexpr int u = decltype(uc)::value;
-      if (u < U) {
-        const bool valid = i0 + 64 * u + lane < i1;
-        const uint32_t x = fresh(key[u]);
-        gt_w += __popcll(__ballot(valid && x > T));
-        eq_w += __popcll(__ballot(valid && x == T));
-      }
+      const bool valid = i0 + 64 * u + lane < i1;
+      const uint32_t x = fresh(key[u]);
+      gt_w += __popcll(__ballot(valid && x > T));
+      eq_w += __popcll(__ballot(valid && x == T));
     });
     if (lane == 0) {
       rs->gt[wv] = (uint32_t)gt_w;
@@ -1636,8 +1620,331 @@ __device__ __forceinline__ void select_regs(const ChunkCands &src, int n, int k,
     if (v < wv) gt_b += (int)rs->gt[v];
     kmax = rs->wmax[v] > kmax ? rs->wmax[v] : kmax;
   }
-  reg_emit<UMAX>(key, shr, 0, T, need_eq, eq_b, gt_b + min(eq_b, need_eq), k, ties, pos_l, irow,
-                 vrow, weights, key2f(kmax), weight_factor(scale));
+  reg_emit<UMAX>(key, shr, T, need_eq, eq_b, gt_b + min(eq_b, need_eq), k, ties,
+                 [&](int i) { return pos_l[i]; }, irow, vrow, weights, key2f(kmax),
+                 weight_factor(scale));
+}
+
+// ---------------------------------------------------------------------------
+// Exact top-k of a full score row by one workgroup (sparse_decode_topk, and
+// fused calls whose rows are selected from full scores).  Bound by latency:
+// every pass over global memory is a round trip of one compute unit, so the
+// row is read once.  A row of at most NT * kRowSlots scores stays in
+// registers; a longer one (1024 threads, at most 1M positions) is filtered
+// as it streams by a threshold taken from a 2048-score sample, its
+// candidates (score, 16-bit offset) kept in LDS.  (Reading them again from
+// the row instead, for room for more of them, took 4 us: a gather of single
+// words passes one cache line per lane.)  Either way the k-th largest key
+// then comes from histograms over the registers.  Four radix passes over the row (select_and_write) remain for
+// rows with too many candidates for the registers, and for a sample that
+// misjudged the row.  64 rows of 50K scores, k = 2501, scores written: 213 us
+// by radix passes of 256 threads, 23 us in this form; one row of 4096, k =
+// 410: 15.2 -> 9.0 us.
+// ---------------------------------------------------------------------------
+constexpr int kRankMax = 64;   // keys of a bucket worth an exact rank count
+constexpr int kRowSlots = 16;  // scores per thread of a row kept whole in registers
+
+// A score's key, never 0: lanes without an item hold key 0, below every
+// bucket and threshold of the functions below.
+__device__ __forceinline__ uint32_t row_key(float f) {
+  const uint32_t x = f2key(f);
+  return x > 1u ? x : 1u;
+}
+
+// Count a wave's items (lanes with in) into hist[bk].  One add where they
+// share a bucket (masked or tied scores): 64 adds to one word run one by one.
+__device__ __forceinline__ void wave_hist(uint32_t *hist, int bk, bool in) {
+  const uint64_t am = __ballot(in);
+  if (!am) return;
+  const int v = __builtin_amdgcn_readlane(bk, __ffsll((unsigned long long)am) - 1);
+  if (__ballot(in && bk == v) == am) {
+    if (lane_id() == 0) atomicAdd(&hist[v], (uint32_t)__popcll(am));
+  } else if (in) {
+    atomicAdd(&hist[bk], 1u);
+  }
+}
+
+// The block's items are the nonzero keys of slots u < U; hist holds their
+// counts in the buckets kb, published.  Returns the bucket [blo, bhi] of the
+// krem-th largest key, narrowed by further histograms until it holds at most
+// mmax keys or one key value, and the keys it holds; krem becomes the rank
+// inside it.  Keys past the last bucket of kb are counted in it.  hist2:
+// zero and published too.  Ends with a barrier.
+template <int NT, int UMAX>
+__device__ __forceinline__ int narrow_bucket(const uint32_t (&key)[UMAX], int U, KeyBuckets kb,
+                                             int mmax, int &krem, uint32_t &blo, uint32_t &bhi,
+                                             uint32_t *hist, uint32_t *hist2, SelShared *sh) {
+  bhi = 0xFFFFFFFFu;
+  for (;;) {
+    find_rank_bin<NT>(hist, kBuckets, krem, sh);
+    const uint32_t b = sh->digit;
+    const int m = (int)hist[b];
+    krem -= sh->above;
+    blo = kb.lo + (b << kb.shift);
+    if (b < (uint32_t)kBuckets - 1u) bhi = blo + ((1u << kb.shift) - 1u);  // (else the range's end)
+    if (m <= mmax || blo == bhi) {
+      __syncthreads();  // sh is reused
+      return m;
+    }
+    kb = KeyBuckets::make(blo, bhi - blo);
+    unroll_slots<UMAX>(U, [&](auto uc) {
+      constexpr int u = decltype(uc)::value;
+      const uint32_t x = fresh(key[u]);
+      wave_hist(hist2, kb.of(x), x >= blo && x <= bhi);
+    });
+    __syncthreads();
+    // (a third level, rare, needs its histogram cleared)
+    for (int i = threadIdx.x; i < kBuckets; i += NT) hist[i] = 0;
+    uint32_t *t = hist;
+    hist = hist2;
+    hist2 = t;
+  }
+}
+
+// The top k (1 <= k <= items) of the keys that the waves hold in item order
+// (share sh: slots u < sh.U, items sh.i0 + 64 u + lane < sh.i1; key 0 past
+// them), written as reg_emit does, from their counts in the buckets kb.
+// vmax: the largest of them (with weights).
+template <int NT, int UMAX, class PosOf>
+__device__ __forceinline__ void reg_select(const uint32_t (&key)[UMAX], const RegShare &sh, int k,
+                                           KeyBuckets kb, uint32_t *hist, uint32_t *hist2,
+                                           SelShared *ss, BucketShared<NT> *bs,
+                                           RegSelShared<NT> *rs, PosOf pos, int32_t *irow,
+                                           float *vrow, bool weights, float vmax, float scale) {
+  const int lane = lane_id(), wv = wave_id();
+  int krem = k;
+  uint32_t blo, bhi;
+  if (threadIdx.x == 0) bs->n = 0;  // (published by narrow_bucket's barriers)
+  const int m = narrow_bucket<NT, UMAX>(key, sh.U, kb, kRankMax, krem, blo, bhi, hist, hist2, ss);
+  uint32_t T = blo;  // (a bucket of one key value)
+  int need_eq = krem;
+  if (blo != bhi) {  // at most kRankMax keys
+    unroll_slots<UMAX>(sh.U, [&](auto uc) {
+      constexpr int u = decltype(uc)::value;
+      const uint32_t x = fresh(key[u]);
+      if (x >= blo && x <= bhi) bs->items[atomicAdd(&bs->n, 1)] = x;
+    });
+    __syncthreads();
+    rank_items(bs->items, m, krem, ss);
+    __syncthreads();
+    T = ss->digit;
+    need_eq = krem - ss->above;
+  }
+  // Kept keys of the waves before this one, then the own ones in item order.
+  int gt_w = 0, eq_w = 0;
+  unroll_slots<UMAX>(sh.U, [&](auto uc) {
+    constexpr int u = decltype(uc)::value;
+    const uint32_t x = fresh(key[u]);
+    gt_w += __popcll(__ballot(x > T));
+    eq_w += __popcll(__ballot(x == T));
+  });
+  if (lane == 0) {
+    rs->gt[wv] = (uint32_t)gt_w;
+    rs->eq[wv] = (uint32_t)eq_w;
+  }
+  __syncthreads();
+  int gt_b = 0, eq_b = 0;
+#pragma unroll
+  for (int v = 0; v < NT / 64; ++v)
+    if (v < wv) {
+      gt_b += (int)rs->gt[v];
+      eq_b += (int)rs->eq[v];
+    }
+  reg_emit<UMAX, PosOf, false>(key, sh, T, need_eq, eq_b, gt_b + min(eq_b, need_eq), k, eq_w > 0,
+                               pos, irow, vrow, weights, vmax, weight_factor(scale));
+}
+
+// Dynamic LDS (bytes) of row_select for rows of up to n scores: a second
+// histogram, and for long rows every candidate's score and offset in its
+// wave's share (as many as the workgroup's 160 KB leave room for).
+constexpr int kRowShareMax = 65536;
+constexpr int kRowCands = 22;  // candidates per thread of a long row
+constexpr int64_t kRowDirectMax = 1024 * kRowSlots;
+constexpr size_t row_select_lds(int64_t n) {
+  return kBuckets * 4 + (n > kRowDirectMax ? (size_t)1024 * kRowCands * 6 : 0);
+}
+
+// Samples of a long row of n scores for a top-k of k, and the rank r among
+// them that gives the threshold; 0: its candidates would not fit.
+constexpr int kRowSampleMax = 8192;
+__host__ __device__ inline int row_samples(int64_t n, int64_t k, int &r) {
+  if (n > 16LL * kRowShareMax) return 0;
+  for (int m = kSampleMax; m <= kRowSampleMax && m < n; m *= 4) {
+    const int64_t rr = pilot_rank(k, m, n);
+    r = (int)(rr < kPilotMinRank ? kPilotMinRank : rr);
+    if (5LL * r * n <= 4LL * m * 1024 * kRowCands) return m;
+  }
+  return 0;
+}
+
+// Top k of the n scores at `row`, positions base, base + 1, ...: entries
+// irow[0, k) and, with vrow, the kept scores or (weights) softmax weights.
+// dyn_bytes: dynamic LDS at dyn.  Returns whether vrow is final (weights not
+// formed: the caller turns the scores into weights).  LONG: with the path of
+// long rows.  Every thread of the block must call it.
+template <int NT, bool LONG>
+__device__ __forceinline__ bool row_select(const float *row, uint32_t base, int n, int k,
+                                           uint32_t *hist, SelShared *ss, BucketShared<NT> *bs,
+                                           RegSelShared<NT> *rs, uint32_t (*range)[2],
+                                           uint32_t *dyn, size_t dyn_bytes, int32_t *irow,
+                                           float *vrow, bool weights, float scale) {
+  constexpr int NW = NT / 64;
+  const int tid = threadIdx.x, lane = lane_id(), wv = wave_id();
+  const auto src = uniform_ptr(row);
+  uint32_t *hist2 = dyn;
+  // The row's largest key, from the waves' (with weights).
+  auto row_max = [&]() {
+    uint32_t m = rs->wmax[0];
+#pragma unroll
+    for (int v = 1; v < NW; ++v) m = rs->wmax[v] > m ? rs->wmax[v] : m;
+    return key2f(m);
+  };
+  if (n <= NT * kRowSlots && dyn_bytes >= row_select_lds(0)) {
+    const RegShare sh = reg_share<NT>(0, n);
+    // Every load of the row is issued before the first returns (lanes past
+    // the share's end repeat its last item).  The first histogram is over
+    // the keys' top 11 bits, so that it needs no range.
+    uint32_t key[kRowSlots];
+    unroll_slots<kRowSlots>(sh.U, [&](auto uc) {
+      constexpr int u = decltype(uc)::value;
+      key[u] = __float_as_uint(src[(uint32_t)min(sh.i0 + 64 * u + lane, sh.i1 - 1)]);
+    });
+    for (int i = tid; i < kBuckets; i += NT) {
+      hist[i] = 0;
+      hist2[i] = 0;
+    }
+    __syncthreads();
+    uint32_t mx = 0u;
+    const KeyBuckets kb{0u, 21};
+    unroll_slots<kRowSlots>(sh.U, [&](auto uc) {
+      constexpr int u = decltype(uc)::value;
+      const bool in = sh.i0 + 64 * u + lane < sh.i1;
+      key[u] = in ? row_key(__uint_as_float(fresh(key[u]))) : 0u;
+      mx = key[u] > mx ? key[u] : mx;
+      wave_hist(hist, (int)(key[u] >> 21), in);
+    });
+    mx = wave_max_u32(mx);
+    if (lane == 0) rs->wmax[wv] = mx;
+    __syncthreads();
+    reg_select<NT, kRowSlots>(key, sh, k, kb, hist, hist2, ss, bs, rs,
+                              [&](int i) { return base + (uint32_t)i; }, irow, vrow, weights,
+                              row_max(), scale);
+    return true;
+  }
+  if constexpr (NT == 1024 && LONG) {
+    // The threshold: the r-th largest key of m samples, rounded down within a
+    // bucket of a few samples (rounding down admits more candidates only).
+    // 2048 samples; 8192 where the candidates that so coarse a threshold lets
+    // through would fill more than 4/5 of the room (1M positions at 100x:
+    // 26K against 17K candidates).
+    constexpr int kS = kRowSampleMax / NT, UMAX = kRowCands;
+    int r;
+    const int m = row_samples(n, k, r);
+    const int S = __builtin_amdgcn_readfirstlane(m / NT);
+    if (dyn_bytes >= row_select_lds(kRowDirectMax + 1) && m > 0) {
+      uint32_t sk[kS], mn = 0xFFFFFFFFu, mx = 0u;
+      unroll_slots<kS>(S, [&](auto uc) {
+        constexpr int u = decltype(uc)::value;
+        sk[u] = __float_as_uint(src[(uint32_t)((int64_t)(u * NT + tid) * n / m)]);
+      });
+      for (int i = tid; i < kBuckets; i += NT) {
+        hist[i] = 0;
+        hist2[i] = 0;
+      }
+      unroll_slots<kS>(S, [&](auto uc) {
+        constexpr int u = decltype(uc)::value;
+        sk[u] = row_key(__uint_as_float(sk[u]));
+        mn = sk[u] < mn ? sk[u] : mn;
+        mx = sk[u] > mx ? sk[u] : mx;
+      });
+      block_key_range<NT>(mn, mx, range);
+      const KeyBuckets skb = KeyBuckets::make(mn, mx - mn);
+      unroll_slots<kS>(S, [&](auto uc) {
+        constexpr int u = decltype(uc)::value;
+        wave_hist(hist, skb.of(sk[u]), true);
+      });
+      __syncthreads();
+      int krem = r;
+      uint32_t th, th_hi;
+      narrow_bucket<NT, kS>(sk, S, skb, 8 + r / 8, krem, th, th_hi, hist, hist2, ss);
+      const float theta = key2f(th);
+      const uint32_t smax = mx;
+      for (int i = tid; i < kBuckets; i += NT) {  // (published below)
+        hist[i] = 0;
+        hist2[i] = 0;
+      }
+      // The wave's contiguous share, 16 loads in flight while 16 are filtered.
+      constexpr int kU = 16, kCap = 64 * UMAX;
+      const RegShare sh = reg_share<NT>(0, n);
+      float *cand = (float *)(dyn + kBuckets) + wv * kCap;
+      uint16_t *off = (uint16_t *)(dyn + kBuckets + NT * UMAX) + wv * kCap;
+      const int last = sh.i1 - 1;
+      float a[kU], c[kU];
+      auto load = [&](int b0, float (&v)[kU]) {
+#pragma unroll
+        for (int u = 0; u < kU; ++u) v[u] = src[(uint32_t)min(b0 + 64 * u + lane, last)];
+      };
+      int cnt = 0;
+      auto filter = [&](int b0, const float (&v)[kU]) {
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          const int i = b0 + 64 * u + lane;
+          const bool pass = i <= last && v[u] >= theta;
+          const uint64_t pm = __ballot(pass);
+          const int at = cnt + lanes_below(pm);
+          if (pass && at < kCap) {
+            cand[at] = v[u];
+            off[at] = (uint16_t)(i - sh.i0);
+          }
+          cnt += __popcll(pm);
+        }
+      };
+      if (sh.i0 < sh.i1) {  // wave-uniform
+        load(sh.i0, a);
+        for (int b0 = sh.i0; b0 < sh.i1; b0 += 2 * 64 * kU) {
+          load(b0 + 64 * kU, c);
+          filter(b0, a);
+          load(b0 + 2 * 64 * kU, a);
+          filter(b0 + 64 * kU, c);
+        }
+      }
+      cnt = __builtin_amdgcn_readfirstlane(cnt);
+      if (lane == 0) rs->gt[wv] = (uint32_t)cnt;
+      __syncthreads();
+      int total = 0;
+      bool room = true;
+#pragma unroll
+      for (int v = 0; v < NW; ++v) {
+        total += (int)rs->gt[v];
+        room = room && (int)rs->gt[v] <= kCap;
+      }
+      if (room && total >= k) {  // uniform: then every score >= the k-th passed
+        const RegShare cs{0, cnt, (cnt + 63) >> 6};
+        uint32_t key[UMAX];
+        // Buckets from the threshold to the largest sample (keys above it
+        // join the top one).
+        const KeyBuckets kb = KeyBuckets::make(th, smax - th);
+        uint32_t cmx = 0u;
+        unroll_slots<UMAX>(cs.U, [&](auto uc) {
+          constexpr int u = decltype(uc)::value;
+          const bool in = 64 * u + lane < cnt;
+          key[u] = in ? row_key(cand[64 * u + lane]) : 0u;
+          cmx = key[u] > cmx ? key[u] : cmx;
+          wave_hist(hist, kb.of(key[u]), in);
+        });
+        cmx = wave_max_u32(cmx);
+        if (lane == 0) rs->wmax[wv] = cmx;
+        __syncthreads();
+        reg_select<NT, UMAX>(key, cs, k, kb, hist, hist2, ss, bs, rs,
+                             [&](int i) { return base + (uint32_t)(sh.i0 + (int)off[i]); }, irow,
+                             vrow, weights, row_max(), scale);
+        return true;
+      }
+      __syncthreads();  // (the counts are read before the LDS is reused)
+    }
+  }
+  select_and_write<NT>(DenseSrc{row, base}, n, k, hist, ss, irow, vrow);
+  return false;
 }
 
 // Per-head rows of the fused path: turn the kept scores (vrow[0..k), written
@@ -1692,7 +1999,7 @@ __device__ __forceinline__ void piece_directory(const Work &w, int row, int c0, 
   const int lane = (int)threadIdx.x;
   const int2 d = lane < nc ? w.dir[(int64_t)row * w.nchunk + c0 + lane] : make_int2(0, 0);
   const int v = d.y > 0 ? d.y : 0;
-  const int inc = wave_incl_scan_dpp(v);
+  const int inc = wave_incl_scan(v);
   if (lane < nc) {
     pre[lane] = inc - v;
     start[lane] = d.x;
@@ -1759,11 +2066,7 @@ __device__ __forceinline__ void piece_hist(const Params &p, const Work &w, int r
     load_keys(base, key);
     count(base, key);
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const uint32_t t = (uint32_t)__shfl_xor((int)mx, o);
-    mx = t > mx ? t : mx;
-  }
+  mx = wave_max_u32(mx);
   if (lane_id() == 0) atomicMax(&sh.kmax, mx);
   __syncthreads();
   // The record; then each run's first slot in the copy, from the top run.
@@ -1774,7 +2077,7 @@ __device__ __forceinline__ void piece_hist(const Params &p, const Work &w, int r
       rec[64] = (uint32_t)n;
       rec[65] = sh.kmax;
     }
-    const int inc = wave_incl_scan_dpp((int)c);
+    const int inc = wave_incl_scan((int)c);
     sh.runs[63 - tid] = (uint32_t)inc - c;
   }
   __syncthreads();
@@ -1874,7 +2177,7 @@ __device__ __forceinline__ bool piece_select(const Params &p, const Work &w, int
   for (int h = 0; h < 2; ++h) {
     const int q = wv + h * NW;
     if (q < P) {
-      suf[q * 64 + 63 - lane] = (uint32_t)wave_incl_scan_dpp((int)c2[h]);
+      suf[q * 64 + 63 - lane] = (uint32_t)wave_incl_scan((int)c2[h]);
       atomicAdd(&colsum[63 - lane], c2[h]);
     }
   }
@@ -1893,7 +2196,7 @@ __device__ __forceinline__ bool piece_select(const Params &p, const Work &w, int
       km = t > km ? t : km;
     }
     const uint32_t v = colsum[63 - lane];
-    const int inc = wave_incl_scan_dpp((int)v);
+    const int inc = wave_incl_scan((int)v);
     const uint64_t hit = __ballot(inc >= k);
     const bool ok = nmax <= kPselItemsMax && ntot >= k && hit != 0 && __ballot(gflag != 0) == 0;
     const int l = hit ? __ffsll((unsigned long long)hit) - 1 : 0;
@@ -1905,7 +2208,7 @@ __device__ __forceinline__ bool piece_select(const Params &p, const Work &w, int
       rq = (int)suf[lane * 64 + run] - above;
       aq[lane] = above;
     }
-    const int ri = wave_incl_scan_dpp(rq);
+    const int ri = wave_incl_scan(rq);
     if (lane < P) ro[lane] = ri - rq;
     if (lane < 32) fh[lane] = 0u;
     if (lane == 63) {
@@ -1967,7 +2270,7 @@ __device__ __forceinline__ bool piece_select(const Params &p, const Work &w, int
   // 4. The k-th bucket (first wave, lane j summing bucket 31 - j of the run).
   if (wv == 0) {
     const uint32_t v = lane < 32 ? fh[31 - lane] : 0u;
-    const int inc = wave_incl_scan_dpp((int)v) + ctl[kAboveRun];
+    const int inc = wave_incl_scan((int)v) + ctl[kAboveRun];
     const uint64_t hit = __ballot(lane < 32 && inc >= k);
     const int l = __ffsll((unsigned long long)hit) - 1;
     if (lane == l) {
@@ -1989,18 +2292,11 @@ __device__ __forceinline__ bool piece_select(const Params &p, const Work &w, int
   // count, or by three radix passes over the key bits when the bucket holds
   // more keys than the workgroup has threads.
   if (m <= NT) {
-    if (tid < m) {
-      const uint32_t x = bkeys[tid];
-      int gt = 0, ge = 0;
-      for (int y = 0; y < m; ++y) {
-        const uint32_t v = bkeys[y];
-        gt += v > x ? 1 : 0;
-        ge += v >= x ? 1 : 0;
-      }
-      if (gt < krem && krem <= ge) {
-        ctl[kT] = (int)x;
-        ctl[kAboveT] = gt;
-      }
+    rank_items(bkeys, m, krem, sh);
+    __syncthreads();
+    if (tid == 0) {
+      ctl[kT] = (int)sh->digit;
+      ctl[kAboveT] = sh->above;
     }
   } else {
     uint32_t t;
@@ -2035,14 +2331,12 @@ __device__ __forceinline__ bool piece_select(const Params &p, const Work &w, int
     }
   }
   int gt_w = 0, eq_w = 0;
-  unroll_for<kPselSlots>([&](auto uc) {
+  unroll_slots<kPselSlots>(shr.U, [&](auto uc) {
     constexpr int u = decltype(uc)::value;
-    if (u < shr.U) {
-      const bool valid = shr.i0 + 64 * u + lane < shr.i1;
-      const uint32_t x = fresh(key[u]);
-      gt_w += __popcll(__ballot(valid && x > T));
-      eq_w += __popcll(__ballot(valid && x == T));
-    }
+    const bool valid = shr.i0 + 64 * u + lane < shr.i1;
+    const uint32_t x = fresh(key[u]);
+    gt_w += __popcll(__ballot(valid && x > T));
+    eq_w += __popcll(__ballot(valid && x == T));
   });
   if (lane == 0) {
     rs->gt[wv] = (uint32_t)gt_w;
@@ -2057,9 +2351,9 @@ __device__ __forceinline__ bool piece_select(const Params &p, const Work &w, int
       eq_b += (int)rs->eq[v];
     }
   // 8. The own kept keys in position order.
-  reg_emit<kPselSlots>(key, shr, 0, T, need_eq, eq_b, gt_b + min(eq_b, need_eq), k, eq_w > 0,
-                       pos_l, irow, vrow, weights, key2f((uint32_t)ctl[kKmax]),
-                       weight_factor(p.scale));
+  reg_emit<kPselSlots>(key, shr, T, need_eq, eq_b, gt_b + min(eq_b, need_eq), k, eq_w > 0,
+                       [&](int i) { return pos_l[i]; }, irow, vrow, weights,
+                       key2f((uint32_t)ctl[kKmax]), weight_factor(p.scale));
   return true;
 }
 
@@ -2070,7 +2364,8 @@ __device__ __forceinline__ bool piece_select(const Params &p, const Work &w, int
 // one-workgroup instances keep their register allocation).
 template <int MODE, int NT, bool PIECES = false>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_select(Params p, Work w, const float *dense, int64_t ld,
-                                               int32_t *idx, float *vals, int lds_cap) {
+                                               int32_t *idx, float *vals, int lds_cap,
+                                               size_t dyn_bytes) {
   extern __shared__ uint32_t dyn[];
   __shared__ uint32_t hist[2048];
   __shared__ SelShared sh;
@@ -2079,7 +2374,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
   __shared__ BucketShared<NT> bs;
   __shared__ RegSelShared<NT> rsh;
   bool weights_done = false;
-  const int row = MODE == 0 ? ordered_row(w, (int)blockIdx.x, p.R) : (int)blockIdx.x;
+  const int row = MODE != 1 ? ordered_row(w, (int)blockIdx.x, p.R) : (int)blockIdx.x;
   const int b = row / p.R;
   const int L = seq_len(p, b);
   // The row's list: its forced sinks, the exact top-k of [lo, hi), then its
@@ -2095,12 +2390,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
   float *vrow = lvals ? lvals + rp.ns : nullptr;
   const int tid = threadIdx.x;
   if (k > 0) {
-    if (MODE == 0 && w.flags[row]) {  // the exact fallback: full scores
+    if (MODE == 2 || (MODE == 0 && w.flags[row])) {  // the exact fallback: full scores
       if (blockIdx.y > 0) return;  // (one workgroup per row)
       if (tid == 0) atomicAdd(&w.stats[0], 1);
       if (!w.dsel_parts)  // (else the k_dsel kernels wrote the selection)
-        select_and_write<NT>(DenseSrc{w.dense + (int64_t)row * p.ncap + rp.lo, (uint32_t)rp.lo},
-                             rp.hi - rp.lo, k, hist, &sh, irow, vrow);
+        weights_done = row_select<NT, MODE != 0>(w.dense + (int64_t)row * p.ncap + rp.lo, (uint32_t)rp.lo,
+                                                  rp.hi - rp.lo, k, hist, &sh, &bs, &rsh, range,
+                                                  dyn, dyn_bytes, irow, vrow, weights, p.scale);
     } else if (MODE == 0 && [&] {
                  if constexpr (PIECES)
                    return piece_select<NT>(p, w, row, L, k, irow, vrow, weights, dyn, hist, &sh,
@@ -2156,8 +2452,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
       weights_done = true;
       }
     } else {
-      select_and_write<NT>(DenseSrc{dense + (int64_t)row * ld + rp.lo, (uint32_t)rp.lo},
-                           rp.hi - rp.lo, k, hist, &sh, irow, vrow);
+      row_select<NT, true>(dense + (int64_t)row * ld + rp.lo, (uint32_t)rp.lo, rp.hi - rp.lo, k,
+                           hist, &sh, &bs, &rsh, range, dyn, dyn_bytes, irow, vrow, false, 0.f);
     }
     if (weights && !weights_done) kept_scores_to_weights<NT>(vrow, k, p.scale, ftmp);
   }
@@ -2173,7 +2469,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
   for (int i = rp.total + tid; i < ist; i += NT) lrow[i] = -1;
   if (lvals)
     for (int i = rp.total + tid; i < p.k_max; i += NT) lvals[i] = -__builtin_inff();
-  if (MODE == 0 && w.ustart) {
+  if (MODE != 1 && w.ustart) {
     // Union attention: where each chunk of union_chunk positions begins in
     // this row's (ascending) list; entry `total` closes the last chunk.
     __syncthreads();  // the list was written by every thread of the block
@@ -2998,6 +3294,18 @@ size_t select_lds_budget(bool wide) {
   return wide ? 144 * 1024 : 150 * 1024;
 }
 
+// Rows of at most 4K scores fit the registers of 256 threads; with two or
+// more rows per compute unit such workgroups run side by side, while fewer
+// rows finish sooner on 1024 threads.
+static bool row_narrow(int64_t rows, int64_t n) {
+  return rows >= 512 && n <= kBlock * kRowSlots;
+}
+
+bool row_selects(int64_t n, int64_t k) {
+  int r;
+  return n <= kRowDirectMax || row_samples(n, k, r) > 0;
+}
+
 hipError_t launch_select_candidates(const Params &p, const Work &w, int32_t *idx, int lds_cap,
                                     bool wide, hipStream_t st) {
   const size_t lds = select_lds_bytes(w.nchunk, lds_cap);
@@ -3005,14 +3313,20 @@ hipError_t launch_select_candidates(const Params &p, const Work &w, int32_t *idx
   // The kept scores / weights only serve an attention that does not
   // recompute its logits.
   float *vals = attend_recompute(true, p) ? nullptr : w.sigma;
-  if (w.psel_parts > 0) {  // (wide: the host asks for pieces only then)
+  if (w.force_repair) {
+    const size_t rlds = row_select_lds(p.ncap);
+    if (row_narrow(rows, p.ncap))
+      k_select<2, kBlock><<<rows, kBlock, rlds, st>>>(p, w, nullptr, 0, idx, vals, 0, rlds);
+    else
+      k_select<2, 1024><<<rows, 1024, rlds, st>>>(p, w, nullptr, 0, idx, vals, 0, rlds);
+  } else if (w.psel_parts > 0) {  // (wide: the host asks for pieces only then)
     const size_t plds = psel_lds_bytes(1024);
     k_select<0, 1024, true><<<dim3(rows, (unsigned)w.psel_parts), 1024, lds > plds ? lds : plds, st>>>(
-        p, w, nullptr, 0, idx, vals, lds_cap);
+        p, w, nullptr, 0, idx, vals, lds_cap, lds > plds ? lds : plds);
   } else if (wide)
-    k_select<0, 1024><<<rows, 1024, lds, st>>>(p, w, nullptr, 0, idx, vals, lds_cap);
+    k_select<0, 1024><<<rows, 1024, lds, st>>>(p, w, nullptr, 0, idx, vals, lds_cap, lds);
   else
-    k_select<0, kBlock><<<rows, kBlock, lds, st>>>(p, w, nullptr, 0, idx, vals, lds_cap);
+    k_select<0, kBlock><<<rows, kBlock, lds, st>>>(p, w, nullptr, 0, idx, vals, lds_cap, lds);
   return hipGetLastError();
 }
 
@@ -3223,7 +3537,12 @@ hipError_t launch_score_dense(const Params &p, float *scores, hipStream_t st) {
 hipError_t launch_topk(const Params &p, const float *scores, int32_t *idx, float *vals,
                        hipStream_t st) {
   Work none{};
-  k_select<1, kBlock><<<p.B * p.R, kBlock, 0, st>>>(p, none, scores, p.ncap, idx, vals, 0);
+  const unsigned rows = (unsigned)(p.B * p.R);
+  const size_t lds = row_select_lds(p.ncap);
+  if (row_narrow(rows, p.ncap))
+    k_select<1, kBlock><<<rows, kBlock, lds, st>>>(p, none, scores, p.ncap, idx, vals, 0, lds);
+  else
+    k_select<1, 1024><<<rows, 1024, lds, st>>>(p, none, scores, p.ncap, idx, vals, 0, lds);
   return hipGetLastError();
 }
 

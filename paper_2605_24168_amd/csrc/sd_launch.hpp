@@ -24,6 +24,9 @@ size_t select_lds_bytes(int nchunk, int lds_cap);
 bool select_wide(const Params &p, size_t lds_bytes);
 // Dynamic LDS available to the candidate selection at that width.
 size_t select_lds_budget(bool wide);
+// Whether one workgroup selects the top k of a full row of n scores in one
+// pass (a row kept in registers, or filtered by a sampled threshold).
+bool row_selects(int64_t n, int64_t k);
 hipError_t launch_select_candidates(const Params &p, const Work &w, int32_t *idx, int lds_cap,
                                     bool wide, hipStream_t st);
 hipError_t launch_repair(const Params &p, const Work &w, hipStream_t st);

@@ -1,0 +1,106 @@
+"""Top-k of full score rows by one workgroup per row: rows that stay in
+registers, rows filtered as they stream by a sampled threshold, and rows that
+take the radix passes, at the sizes where one form gives way to the next, for
+score distributions that crowd or break the histograms (ties, masked rows,
+infinities, one cluster, sorted rows), and the fused calls that select from
+full scores.  Lists and scores must equal the oracle's selection on the same
+float32 scores exactly.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2605_24168_amd import synth
+from tests import parity as P
+from tests.test_gpu_parity import check_fused
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sd():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2605_24168_amd import sparse_decode
+    sparse_decode.set_debug(0)
+    return sparse_decode
+
+
+def rows_of_kind(kind, rows, n):
+    rng = np.random.default_rng(n * 31 + rows)
+    s = rng.standard_normal((rows, n), dtype=np.float32)
+    if kind == "ties":
+        s = np.round(2 * s)
+    elif kind == "masked":
+        s[rng.random(s.shape) < 0.99] = -np.inf
+    elif kind == "lowest":
+        s[rng.random(s.shape) < 0.5] = np.finfo(np.float32).min
+    elif kind == "inf":
+        s[rng.random(s.shape) < 0.2] = np.inf
+    elif kind == "cluster":  # one wave's share holds most of the candidates
+        s[:, n // 2:n // 2 + n // 20] += 6
+    elif kind == "sorted":
+        s.sort(axis=1)
+    elif kind == "zeros":
+        s = np.where(s < 0, np.float32(-0.0), np.float32(0.0))
+    return s
+
+
+def check(sd, s, L, ratio, n_sink=0, n_local=0):
+    rows, n = s.shape
+    sp = sd.Sparsity(ratio=ratio, n_sink=n_sink, n_local=n_local)
+    idx, vals = sd.sparse_decode_topk(torch.from_numpy(s[None]).cuda(),
+                                      torch.tensor([L], dtype=torch.int32, device="cuda"), sp,
+                                      with_vals=True)
+    torch.cuda.synchronize()
+    idx, vals = idx[0].cpu().numpy(), vals[0].cpu().numpy()
+    ns = min(n_sink, L)
+    nl = min(n_local, L - ns)
+    k = min(O.budget(L, ratio, 0), L - ns - nl)
+    for r in range(rows):
+        # (score descending, position ascending), as a stable sort gives it
+        top = np.sort(np.argsort(-s[r, ns:L - nl], kind="stable")[:k]) + ns
+        want = np.concatenate([np.arange(ns), top, np.arange(L - nl, L)])
+        assert np.array_equal(idx[r, :want.size], want), (r, L, ratio)
+        assert (idx[r, want.size:] == -1).all()
+        assert np.array_equal(vals[r, :want.size], s[r, want])
+        assert (vals[r, want.size:] == -np.inf).all()
+
+
+@pytest.mark.parametrize("kind", ["normal", "ties", "masked", "lowest", "inf", "cluster", "sorted",
+                                  "zeros"])
+@pytest.mark.parametrize("rows,n,ratio", [
+    (3, 1, 1.0), (3, 65, 4.0), (2, 1025, 10.0),
+    (513, 4096, 20.0), (513, 4097, 20.0),        # 256-thread rows, and past them
+    (2, 16384, 20.0), (2, 16385, 20.0),          # in registers, and past them
+    (2, 50021, 9.0), (2, 50021, 1.5),            # filtered; too many candidates
+    (2, 131072, 11.0), (1, 1048576, 100.0), (1, 1048577, 100.0),  # 8192 samples; 16-bit offsets end
+])
+def test_topk_rows(sd, kind, rows, n, ratio):
+    check(sd, rows_of_kind(kind, rows, n), n, ratio)
+
+
+@pytest.mark.parametrize("L", [0, 1, 63, 16500, 50000])
+def test_topk_forced_and_short_sequences(sd, L):
+    if L == 0:
+        sp = sd.Sparsity(ratio=20.0, n_sink=16, n_local=8)
+        idx = sd.sparse_decode_topk(torch.randn((1, 2, 50021), device="cuda"),
+                                    torch.zeros(1, dtype=torch.int32, device="cuda"), sp)
+        assert (idx == -1).all()
+        return
+    check(sd, rows_of_kind("normal", 2, 50021), L, 20.0, n_sink=16, n_local=8)
+
+
+@pytest.mark.parametrize("n,ratio", [
+    (4096, 10.0), (16400, 20.0), (50000, 10.0),  # one workgroup per row
+    (50000, 2.0),                                # several workgroups per row
+])
+def test_fused_rows_from_full_scores(sd, n, ratio):
+    inp = synth.make_inputs(1, seed=5, B=2, Hq=4, Hkv=2, seq_lens=[n, n // 3 + 7], ncap=n + 5,
+                            ratio=ratio)
+    q, cache, lens = sd.cache_from_inputs(inp)
+    out, idx = sd.sparse_decode_attention(q, cache, lens, sd.sparsity_from_inputs(inp),
+                                          k_max=O.k_max_for(inp))
+    torch.cuda.synchronize()
+    check_fused(inp, P.to_host(out), idx.cpu().numpy(), label=f"{n} at {ratio}x")
