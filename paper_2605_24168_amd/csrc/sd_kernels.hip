@@ -966,7 +966,184 @@ __global__ __launch_bounds__(kBlock) void k_score_stream(Params p, Work w) {
 }
 
 // ---------------------------------------------------------------------------
-// Full scores of one (sequence b, KV head g): part `part` of `parts` takes
+// Full scores of bf16 keys, streamed: a wave takes a run of consecutive
+// 64-key blocks of one (sequence, KV head), four 16-key tiles each, kept in
+// flight as a ring (a tile's registers are loaded again as soon as it is
+// staged), scored by the matrix ops of mfma_scores, and writes each head's 64
+// scores of a block as one 256-byte run (the result layout holds 16 keys of
+// a head side by side, and 64-byte stores far apart in time cost the read
+// stream more than their bytes).  Bound by HBM: 256 bytes read and 4 per row
+// of the group written per key.  Runs are as long as leaves about
+// kScoreWaves waves: 16 groups of 50K keys (205 MB): 83 us with 8192 keys to
+// a workgroup (112 workgroups), loaded in the operand layout.
+// ---------------------------------------------------------------------------
+constexpr int kScoreBlock = 64;       // keys of a block
+constexpr int kScoreRunMax = 32;      // blocks of a run, at most
+constexpr int kScoreWaves = 4096;     // waves to spread a call over
+constexpr int kScoreLd = kScoreBlock + 4;  // staged row stride: the lane groups on distinct banks
+
+struct ScoreLds {
+  u32x4 tile[256];
+  float out[kMaxGroup * kScoreLd];
+  int32_t page[kScoreRunMax * kScoreBlock / kTile];
+};
+
+// The runs of a call: blocks per run, runs per (sequence, KV head).
+struct ScoreRuns {
+  int blocks, runs;
+  __host__ __device__ ScoreRuns(int64_t ncap, int64_t groups) {
+    const int64_t nblk = (ncap + kScoreBlock - 1) / kScoreBlock;
+    int64_t per = (nblk * groups + kScoreWaves - 1) / kScoreWaves;
+    per = per < 1 ? 1 : (per > kScoreRunMax ? kScoreRunMax : per);
+    blocks = (int)per;
+    runs = (int)((nblk + per - 1) / per);
+  }
+};
+
+// NR: rows of the group rounded up to 1, 2, 4, 8 or 16 (1 group-shared); rows
+// past the last repeat it, so that every block issues the same stores and
+// the waits for the loads between them stay exact.  Scores of the run's keys
+// below L; none when it starts past them.
+template <bool PAGED, bool GRP, int NR>
+__device__ __forceinline__ void score_run(const Params &p, float *dst, int64_t ld, int b, int g,
+                                          int64_t j0, int nkeys, int L, ScoreLds &wl) {
+  if (j0 >= L) return;
+  const int n = (int)(L - j0 < nkeys ? L - j0 : nkeys);
+  const int l = lane_id(), col = l & 15, a = l >> 4;
+  const int nrows = GRP ? 1 : p.G;
+  float *out = dst + (GRP ? (int64_t)b * p.R + g : (int64_t)b * p.R + (int64_t)g * p.G) * ld + j0;
+  QFrag qf;
+  load_q_bf16(p, b, g, qf);
+  const int ntiles = (n + kTile - 1) / kTile, last = n - 1;
+  if (PAGED) {
+    const int32_t *bt = p.K.block_table + (int64_t)b * p.K.max_pages + (j0 >> 4);
+    for (int i = l; i < ntiles; i += 64) wl.page[i] = bt[i];
+    __builtin_amdgcn_wave_barrier();  // every lane reads every page id
+  }
+  constexpr int64_t kRowBytes = kHeadDim * 2;
+  const char *kbase = (const char *)p.K.base;
+  const char *slab = kbase + (((int64_t)b * p.K.hkv + g) * p.K.ncap + j0) * kRowBytes;
+  const int64_t page_bytes = (int64_t)kTile * p.K.hkv * kRowBytes;
+  auto load = [&](int ti, u32x4 v[4]) {
+    ti = ti < ntiles ? ti : ntiles - 1;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      int j = ti * kTile + 4 * t + a;
+      j = j < last ? j : last;
+      const char *row = PAGED ? kbase + wl.page[ti] * page_bytes + ((int64_t)(j & 15) * p.K.hkv + g) * kRowBytes
+                              : slab + (int64_t)j * kRowBytes;
+      v[t] = __builtin_nontemporal_load((const u32x4 *)(row + 16 * swz_chunk(t)));
+    }
+  };
+  constexpr int kB = kScoreBlock / kTile;
+  u32x4 buf[kB][4];
+#pragma unroll
+  for (int u = 0; u < kB; ++u) {
+    load(u, buf[u]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  auto block = [&](int tb) {
+#pragma unroll
+    for (int u = 0; u < kB; ++u) {
+      stage_tile(wl.tile, buf[u]);
+      load(tb + u + kB, buf[u]);
+      __builtin_amdgcn_wave_barrier();  // the tile is read back by other lanes
+      KFrag kf;
+      read_kfrag(wl.tile, kf);
+      __builtin_amdgcn_wave_barrier();  // and overwritten by the next one
+      f32x4 acc = mfma_scores(qf, kf);
+      if constexpr (GRP) {
+        const float gs = group_sum(acc);
+        if (a == 0) wl.out[16 * u + col] = gs;
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (4 * a + r < NR) wl.out[(4 * a + r) * kScoreLd + 16 * u + col] = acc[r];
+      }
+    }
+    __builtin_amdgcn_wave_barrier();  // the scores are read by other lanes
+  };
+  const int nblk = n / kScoreBlock;
+  for (int k = 0; k < nblk; ++k) {
+    block(k * kB);
+#pragma unroll
+    for (int h = 0; h < NR; ++h) {
+      const int hh = h < nrows ? h : nrows - 1;
+      out[hh * ld + (int64_t)k * kScoreBlock + l] = wl.out[hh * kScoreLd + l];
+    }
+    __builtin_amdgcn_wave_barrier();  // and overwritten by the next block
+  }
+  if (n % kScoreBlock) {
+    block(nblk * kB);
+    const int j = nblk * kScoreBlock + l;
+    for (int h = 0; h < nrows; ++h)
+      if (j < n) out[h * ld + j] = wl.out[h * kScoreLd + l];
+  }
+}
+
+// What the fused path's later kernels expect where this one is its first (a
+// call whose every row is selected from full scores): the repaired-row count
+// reset, every row with a budget flagged, and the multi-workgroup selection's
+// histograms cleared.
+struct ScoreInit {
+  int32_t *stats, *flags;
+  uint32_t *hist;  // null: none
+};
+
+// sparse_decode_score over bf16 keys, and the scoring of a fused call forced
+// onto full scores (init.stats set): grid = (runs of a workgroup's four
+// waves) x groups, 1-D.  The waves of a workgroup take consecutive runs of
+// one head, a head's slab swept in order; in the paged layout heads go
+// fastest and, with a multiple of 4 of them, the waves take four heads of
+// the same run (a position's heads are adjacent in a page).  fill: positions
+// past the sequence get -inf.
+template <bool PAGED, bool GRP, int NR>
+__global__ __launch_bounds__(kBlock) void k_score_keys(Params p, float *dst, int64_t ld, int blocks,
+                                                       int runs, int fill, ScoreInit init) {
+  __shared__ ScoreLds sl[kWaves];
+  if (init.stats) {
+    const int64_t rows = (int64_t)p.B * p.R, all = (int64_t)gridDim.x * kBlock;
+    const int64_t e0 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (e0 == 0) init.stats[0] = 0;
+    for (int64_t e = e0; e < rows; e += all) {
+      const int bb = (int)(e / p.R);
+      init.flags[e] = row_plan(p, bb, seq_len(p, bb)).kh > 0 ? 1 : 0;
+    }
+    if (init.hist)
+      for (int64_t e = e0; e < rows * 2048; e += all) init.hist[e] = 0u;
+  }
+  const int wid = (int)blockIdx.x, wv = __builtin_amdgcn_readfirstlane(wave_id());
+  int b, g, run;
+  const int rw = (runs + kWaves - 1) / kWaves;
+  if (PAGED && p.Hkv % kWaves == 0) {
+    const int nq = p.Hkv / kWaves;
+    g = kWaves * (wid % nq) + wv;
+    run = (wid / nq) % runs;
+    b = wid / (nq * runs);
+  } else if (PAGED) {
+    g = wid % p.Hkv;
+    run = kWaves * ((wid / p.Hkv) % rw) + wv;
+    b = wid / (p.Hkv * rw);
+  } else {
+    run = kWaves * (wid % rw) + wv;
+    g = (wid / rw) % p.Hkv;
+    b = wid / (rw * p.Hkv);
+  }
+  if (run >= runs) return;  // (per wave: no block barriers)
+  const int L = seq_len(p, b), nkeys = blocks * kScoreBlock;
+  const int64_t j0 = (int64_t)run * nkeys;
+  score_run<PAGED, GRP, NR>(p, dst, ld, b, g, j0, nkeys, L, sl[wv]);
+  const int64_t end = j0 + nkeys < p.ncap ? j0 + nkeys : p.ncap;
+  if (!fill || end <= L) return;
+  const int64_t from = j0 > L ? j0 : L;
+  const int64_t row0 = GRP ? (int64_t)b * p.R + g : (int64_t)b * p.R + (int64_t)g * p.G;
+  for (int h = 0; h < (GRP ? 1 : p.G); ++h)
+    for (int64_t j = from + lane_id(); j < end; j += 64) dst[(row0 + h) * ld + j] = -__builtin_inff();
+}
+
+// ---------------------------------------------------------------------------
+// Full scores of one (sequence b, KV head g) from labels or float32 keys:
+// part `part` of `parts` takes
 // tiles part*4 + wave, stepping by parts*4.  dst[row][j] for j < L_b; with
 // fill_tail, -inf for L_b <= j < ncap.  Every thread of the block must call
 // it (the f32 scorer stages the queries in LDS behind a barrier).
@@ -3383,7 +3560,16 @@ static bool dense_pipelined(const Params &p, int parts) {
          per_wave >= 2 * dense_depth(p.labels != nullptr);
 }
 
+template <bool PAGED>
+static hipError_t score_keys(const Params &p, float *dst, bool fill, const ScoreInit &init,
+                             hipStream_t st);
+
 hipError_t launch_repair(const Params &p, const Work &w, hipStream_t st) {
+  if (w.force_repair && p.bf16 && !p.labels) {
+    const ScoreInit init{w.stats, w.flags, w.dsel_parts ? w.dsel_hist : nullptr};
+    return p.K.paged ? score_keys<true>(p, w.dense, false, init, st)
+                     : score_keys<false>(p, w.dense, false, init, st);
+  }
   const int parts = repair_parts(p, w);
   const dim3 grid(parts, p.B * p.Hkv);
   const bool pipe = dense_pipelined(p, parts);
@@ -3518,16 +3704,42 @@ hipError_t launch_attend(const Params &p, const Work &w, const int32_t *idx, voi
   return hipGetLastError();
 }
 
+template <bool PAGED, bool GRP, int NR>
+static hipError_t launch_score_keys(const Params &p, float *dst, bool fill, const ScoreInit &init,
+                                    hipStream_t st) {
+  const ScoreRuns r(p.ncap, (int64_t)p.B * p.Hkv);
+  const int64_t rw = (r.runs + kWaves - 1) / kWaves;
+  const int64_t grid = (int64_t)p.B * (PAGED && p.Hkv % kWaves == 0 ? (p.Hkv / kWaves) * (int64_t)r.runs
+                                                                    : p.Hkv * rw);
+  if (grid > INT32_MAX) return hipErrorInvalidConfiguration;
+  k_score_keys<PAGED, GRP, NR><<<(unsigned)grid, kBlock, 0, st>>>(p, dst, p.ncap, r.blocks, r.runs,
+                                                                  fill ? 1 : 0, init);
+  return hipGetLastError();
+}
+
+template <bool PAGED>
+static hipError_t score_keys(const Params &p, float *dst, bool fill, const ScoreInit &init,
+                             hipStream_t st) {
+  if (p.group_shared) return launch_score_keys<PAGED, true, 1>(p, dst, fill, init, st);
+  if (p.G <= 1) return launch_score_keys<PAGED, false, 1>(p, dst, fill, init, st);
+  if (p.G <= 2) return launch_score_keys<PAGED, false, 2>(p, dst, fill, init, st);
+  if (p.G <= 4) return launch_score_keys<PAGED, false, 4>(p, dst, fill, init, st);
+  if (p.G <= 8) return launch_score_keys<PAGED, false, 8>(p, dst, fill, init, st);
+  return launch_score_keys<PAGED, false, 16>(p, dst, fill, init, st);
+}
+
 hipError_t launch_score_dense(const Params &p, float *scores, hipStream_t st) {
+  if (p.bf16 && !p.labels) {
+    const ScoreInit none{nullptr, nullptr, nullptr};
+    return p.K.paged ? score_keys<true>(p, scores, true, none, st)
+                     : score_keys<false>(p, scores, true, none, st);
+  }
   const int parts = (int)cdiv(p.ncap, kDenseChunk);
   const dim3 grid(parts, p.B * p.Hkv);
   const bool pipe = dense_pipelined(p, parts);
   if (p.labels) {
     if (pipe) k_score_dense<true, true, true><<<grid, kBlock, 0, st>>>(p, scores, p.ncap);
     else k_score_dense<true, true, false><<<grid, kBlock, 0, st>>>(p, scores, p.ncap);
-  } else if (p.bf16) {
-    if (pipe) k_score_dense<true, false, true><<<grid, kBlock, 0, st>>>(p, scores, p.ncap);
-    else k_score_dense<true, false, false><<<grid, kBlock, 0, st>>>(p, scores, p.ncap);
   } else {
     k_score_dense<false, false, false><<<grid, kBlock, 0, st>>>(p, scores, p.ncap);
   }
