@@ -261,20 +261,21 @@ bool union_eligible(const Shape &s, const sd_sparsity *sp, bool labels) {
 }
 
 // Whether it is faster than per-head lists: each head's k_max kept rows
-// (key + value, 512 B) against the expected union of G such sets of an
+// (key + value, 512 B; the value alone where the selection's scores are the
+// logits) against the expected union of G such sets of an
 // Ncap-position range drawn independently (heads that agree only shrink the
 // union), plus reading the heads' lists once more.  The group-row
 // kernel gathers at about 0.87 of the per-head kernel's rate for up to 4
 // heads (three waves per SIMD) and 0.7 for more (8 heads per pass: two
 // waves), measured at 128K, so the union must move under 0.83 or 0.65 of
 // the bytes.  Debug flags 4 / 8 force it off / on.
-bool union_pays(const Shape &s, int64_t k_max) {
+bool union_pays(const Shape &s, int64_t k_max, bool labels) {
   const int dbg = g_debug.load();
   if (dbg & 4) return false;
   if (dbg & 8) return true;
   const double Lc = (double)s.ncap, G = s.G;
   const double kt = (double)(k_max < s.ncap ? k_max : s.ncap);
-  const double per_head = G * kt * 512.0;
+  const double per_head = G * kt * (labels ? 512.0 : 256.0);
   const double uni = Lc * (1.0 - std::pow(1.0 - kt / Lc, G)) * 512.0 + 4.0 * G * kt;
   return uni < (s.G <= 4 ? 0.83 : 0.65) * per_head;
 }
@@ -358,7 +359,7 @@ Layout layout_for(const Shape &s, int64_t k_max, bool fused, const sd_sparsity *
   shape_only.n_local = sp->n_local;
   L.nsplit = sd::attend_nsplit(shape_only);
   const bool uni_ok = fused && allow_union && union_eligible(s, sp, labels);
-  if (uni_ok && union_pays(s, k_max)) {
+  if (uni_ok && union_pays(s, k_max, labels)) {
     L.union_chunk = sd::union_chunk(shape_only);
     const int un = (int)((s.ncap + L.union_chunk - 1) / L.union_chunk);
     L.nsplit = un > L.nsplit ? un : L.nsplit;
@@ -849,7 +850,8 @@ sd_status attention_impl(const sd_tensor *q, const sd_kv *K, const sd_kv *V,
   const size_t pre_bytes = sd::select_lds_bytes(L.nchunk, 0);
   const int64_t room256 = (int64_t)sd::select_lds_budget(false) - (int64_t)pre_bytes;
   const bool wide = sd::select_wide(
-      p, pre_bytes + 4 * (size_t)std::max<int64_t>(0, std::min<int64_t>(want, room256 / 4)));
+      p, pre_bytes + 4 * (size_t)std::max<int64_t>(0, std::min<int64_t>(want, room256 / 4)),
+      (int64_t)(fcand * (double)k_max * (1.0 + 1.0 / std::sqrt(rank))));
   const size_t budget = sd::select_lds_budget(wide);
   if (pre_bytes >= budget) return SD_ERR_UNSUPPORTED;
   const int64_t lds_room = (int64_t)((budget - pre_bytes) / 4);
@@ -892,13 +894,10 @@ sd_status attention_impl(const sd_tensor *q, const sd_kv *K, const sd_kv *V,
   if (e == hipSuccess) e = mark(4);
   if (e == hipSuccess && !smp) e = sd::launch_attend(p, w, idx_ptr, out->data, true, stream_h);
   if (e == hipSuccess && smp) {
-    // Weighted attention over the kept entries and the draws, logits
-    // recomputed from the key rows.
+    // Weighted attention over the kept entries and the draws.
     sd::Params pa = p;
-    pa.k_max = (int32_t)k_list;
-    pa.idx_stride = 0;
     pa.weights = smp->weights;
-    e = sd::launch_attend(pa, w, idx_ptr, out->data, false, stream_h);
+    e = sd::launch_attend(pa, w, idx_ptr, out->data, true, stream_h);
   }
   if (e == hipSuccess) e = mark(5);
   if (prof && e == hipSuccess) {

@@ -2309,7 +2309,7 @@ __device__ __forceinline__ bool piece_select(const Params &p, const Work &w, int
   uint32_t *bkeys = runk + kPselRunMax;             // [kPselRunMax] the k-th bucket's keys
   uint32_t *pos_l = bkeys + kPselRunMax;            // [NT * kPselSlots] own positions
   uint8_t *runq = (uint8_t *)(pos_l + NT * kPselSlots);  // [kPselRunMax] their pieces
-  enum { kRun, kAboveRun, kKmax, kR, kOk, kBstar, kKrem, kM, kT, kAboveT, kGtBefore, kEqBefore, kNb };
+  enum { kRun, kAboveRun, kKmax, kR, kOk, kBstar, kKrem, kM, kGtBefore, kEqBefore, kNb };
   const uint32_t *rec0 = w.psel_rec + (int64_t)row * P * kPselStride;
   const int ck = w.chunk_keys;
   const int nch = (L + ck - 1) / ck;
@@ -2470,23 +2470,18 @@ __device__ __forceinline__ bool piece_select(const Params &p, const Work &w, int
   // more keys than the workgroup has threads.
   if (m <= NT) {
     rank_items(bkeys, m, krem, sh);
-    __syncthreads();
-    if (tid == 0) {
-      ctl[kT] = (int)sh->digit;
-      ctl[kAboveT] = sh->above;
-    }
   } else {
     uint32_t t;
     int eq;
     radix_select<NT>(LdsKeys{bkeys}, m, krem, hist, sh, t, eq);
     if (tid == 0) {
-      ctl[kT] = (int)t;
-      ctl[kAboveT] = krem - eq;
+      sh->digit = t;
+      sh->above = krem - eq;
     }
   }
   __syncthreads();
-  const uint32_t T = (uint32_t)ctl[kT];
-  const int need_eq = krem - ctl[kAboveT];
+  const uint32_t T = sh->digit;
+  const int need_eq = krem - sh->above;
   // 7. Kept keys before this piece (above T, equal to T: the pieces'
   // candidates above the run, and the run's keys) and before each wave.
   {
@@ -2557,8 +2552,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
   // The row's list: its forced sinks, the exact top-k of [lo, hi), then its
   // forced local window.
   const RowPlan rp = row_plan(p, b, L);
-  const bool forced = rp.ns + rp.nl > 0;
-  const bool weights = MODE != 1 && !p.group_shared && !forced && vals != nullptr;
+  // (the attention wants finished weights where the list is the top-k alone,
+  // scores where other entries share its softmax)
+  const bool weights = MODE != 1 && p.n_sink + p.n_local == 0 && p.idx_stride == 0 && vals != nullptr;
   const int k = rp.kh;
   const int64_t ist = p.idx_stride > 0 ? p.idx_stride : p.k_max;  // list row stride
   int32_t *lrow = idx + (int64_t)row * ist;
@@ -2904,21 +2900,17 @@ __global__ __launch_bounds__(kBlock) void k_sample_rest(Params p, int32_t *list,
 }
 
 // ---------------------------------------------------------------------------
-// Gather-attend.  grid = (splits, rows).  Workgroup s of row (b, r) takes
-// list entries [s*split, +split) of idx[b][r]; in per-head mode the row is
-// query head r, in group-shared mode it serves the G heads of KV head r.
-// FUSED: the list holds exactly k_b valid positions, and per-head rows take
-// their softmax weights from sigma (formed by the selection); group-shared
-// rows, and every row of the unfused call, recompute each head's logits
-// from the kept key rows (MFMA tiles for bf16), skipping entries outside
-// [0, L_b), and form the weights exp(z - max) once per position in LDS.  Each wave then walks 4 * U positions per step
-// (U per 16-lane group, 16 lanes x 16 bytes covering one 256-byte
-// bf16 value row), with the next step's loads issued before the current
-// step is consumed.  A row split over several workgroups leaves (max, sum,
+// Gather-attend of group rows (group-shared sets, and the group-deduplicated
+// attention).  grid = (splits, rows).  Workgroup s of row (b, r) takes list
+// entries [s*split, +split) of idx[b][r] and serves the G heads of KV head r.
+// Each head's logits are recomputed from the kept key rows (MFMA tiles for
+// bf16), skipping entries outside [0, L_b), and the weights exp(z - max)
+// formed once per position in LDS.  Each wave then walks 4 * U positions per
+// step (U per 16-lane group, 16 lanes x 16 bytes covering one 256-byte bf16
+// value row), with the next step's loads issued before the current step is
+// consumed.  A row split over several workgroups leaves (max, sum,
 // unnormalised output) partials that k_merge combines.
-// Dynamic LDS: voff[split] i64, koff[split] i64 (recompute only),
-// e[nh][split] f32, pos[split] i32, q[nh][128] f32 (recompute only),
-// red[kWaves][nhb][128] f32, lred[kWaves][nhb] f32, nhb = min(nh, kAttHeads).
+// Dynamic LDS: AttLds, nhb = min(nh, kAttHeads).
 // ---------------------------------------------------------------------------
 constexpr int kAttHeads = 8;  // heads accumulated per pass over the value rows
 constexpr int kUnionPerThread = 4;  // union attention: mask positions per thread
@@ -2975,14 +2967,8 @@ __device__ __forceinline__ void store_out(void *out, int64_t off, float v) {
 }
 
 __device__ __forceinline__ int attend_list_len(const Params &p, int b, int L, bool fused) {
-  return fused ? row_plan(p, b, L).total : p.k_max;
-}
-
-// Logits are recomputed from the key rows unless the selection formed the
-// softmax weights already (fused per-head rows on exact scores without
-// forced positions).
-__host__ __device__ inline bool attend_recompute(bool fused, const Params &p) {
-  return !fused || p.group_shared || p.n_sink + p.n_local > 0 || p.labels != nullptr;
+  if (!fused) return p.k_max;
+  return p.idx_stride > 0 ? p.idx_stride : row_plan(p, b, L).total;
 }
 
 // Row index of position j of sequence b in a cache, 32 bits: j itself in
@@ -2999,21 +2985,302 @@ __device__ __forceinline__ int64_t row_offset(const KvView &kv, int b, int g, ui
   return ((int64_t)r * kv.hkv + g) * kHeadDim;
 }
 
+// ---------------------------------------------------------------------------
+// Gather-attend of per-head rows.  grid = (splits, rows), workgroup s of row
+// (b, r), query head r, takes entries [s*split, +split) of its list, each
+// wave a contiguous share of them.
+//   kGatherWeights: the fused call's softmax weights are in sigma.
+//   kGatherScores: the fused call's scores are in sigma for the top-k part of
+//     the list; the entries around it (forced positions, draws) take their
+//     logits from their key rows.
+//   kGatherKeys: every entry's logit from its key row (caller's lists, label
+//     selection).  Entries outside [0, L_b) are skipped.
+// Bound by random 256-byte gathers, so nothing waits on anything but memory:
+// a 16-lane group takes one entry at a time, its key row and value row loaded
+// side by side, the logit summed over the group's lanes and the softmax run
+// online per group, so that the loads of the next 16 entries of a wave are in
+// flight while these are accumulated, with no barrier before the end.  The
+// indices are read 64 at a time, one per lane, two blocks ahead, and their
+// page-table entries one block ahead.  (Logits of a whole split first, then
+// its values, from LDS, moved the same bytes in 176 us instead of 145 at
+// 8 x 32 heads x 6554 of 128K entries with weights, the memory idle at the
+// barriers between.)
+// A row split over several workgroups leaves (max, sum, unnormalised output)
+// partials that k_merge combines.
+// ---------------------------------------------------------------------------
+enum { kGatherWeights, kGatherScores, kGatherKeys };
+constexpr float kLogitFloor = -3.402823466e38f;  // start of a running maximum (finite)
+
+template <bool BF16>
+struct GatherAcc {
+  float m, l, o[8];
+  float q[8];        // float32: this lane's query channels 8 col .. 8 col + 7
+  uint32_t qp[4];    // bf16: the same as bf16 pairs
+};
+
+// Sum over the 16 lanes of a DPP row, in every lane of it.
+__device__ __forceinline__ float row_sum16(float v) {
+  auto ror = [&](auto c) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(
+        0, (int)__float_as_uint(v), decltype(c)::value, 0xf, 0xf, false));
+  };
+  v += ror(std::integral_constant<int, 0x121>{});  // row_ror:1, 2, 4, 8
+  v += ror(std::integral_constant<int, 0x122>{});
+  v += ror(std::integral_constant<int, 0x124>{});
+  v += ror(std::integral_constant<int, 0x128>{});
+  return v;
+}
+
+// Entries [t0, t1) of a list (this wave's, t0 and t1 the same on every lane).
+// KEYS: logits from the key rows, plus log of the entries' weights (wrow, or
+// null).  Otherwise srow holds scores (SCORES) or finished weights.
+template <bool BF16, bool KEYS, bool SCORES>
+__device__ __forceinline__ void gather_entries(const Params &p, int b, int g, int L,
+                                               const int32_t *irow, const float *srow,
+                                               const float *wrow, int t0, int t1,
+                                               GatherAcc<BF16> &st) {
+  if (t0 >= t1) return;
+  constexpr int U = BF16 ? 4 : 2;            // entries per group and batch
+  constexpr int kBatch = 4 * U, kBatches = 64 / kBatch;
+  constexpr int kRow = kHeadDim * (BF16 ? 2 : 4);
+  const int l = lane_id(), col = l & 15, sub = l >> 4;
+  const char *kb = (const char *)p.K.base, *vb = (const char *)p.V.base;
+  // (one table lookup serves keys and values that share their block table)
+  const bool same = !p.K.paged || p.K.block_table == p.V.block_table;
+  const uint32_t slab = (uint32_t)(((int64_t)b * p.K.hkv + g) * p.K.ncap);
+  const int32_t *kt = p.K.block_table + (int64_t)b * p.K.max_pages;
+  const int32_t *vt = p.V.block_table + (int64_t)b * p.V.max_pages;
+  struct Raw {  // a block of 64 entries as read: one per lane
+    int32_t j;
+    float s;
+  };
+  struct Block {  // its rows (counted in rows of the whole cache) and terms
+    uint32_t k, v;
+    float z;
+  };
+  auto fetch = [&](int n, Raw &r) {
+    const int t = t0 + 64 * n + l, tc = t < t1 ? t : t1 - 1;
+    r.j = irow[tc];
+    r.s = KEYS ? (wrow ? wrow[tc] : 1.f) : srow[tc];
+    if (t >= t1) r.j = -1;
+  };
+  auto resolve = [&](const Raw &r, Block &bk) {
+    const bool in = r.j >= 0 && r.j < L;
+    const uint32_t j = in ? (uint32_t)r.j : 0u;
+    if (p.K.paged) {
+      const uint32_t pk = (uint32_t)kt[j >> 4];
+      bk.k = (pk * kTile + (j & 15)) * (uint32_t)p.K.hkv + (uint32_t)g;
+      bk.v = bk.k;
+      if (!same) bk.v = ((uint32_t)vt[j >> 4] * kTile + (j & 15)) * (uint32_t)p.K.hkv + (uint32_t)g;
+    } else {
+      bk.k = bk.v = slab + j;
+    }
+    if (KEYS) bk.z = in && r.s > 0.f ? (wrow ? logf(r.s) : 0.f) : -__builtin_inff();
+    else if (SCORES) bk.z = in ? p.scale * r.s : -__builtin_inff();
+    else bk.z = in ? r.s : 0.f;
+  };
+  // Batch q of a block: group `sub` takes its entries kBatch q + 4 u + sub.
+  auto issue = [&](const Block &bk, int q, RowRaw<BF16> (&k)[KEYS ? U : 1], RowRaw<BF16> (&v)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = kBatch * q + 4 * u + sub;
+      const uint32_t rv = (uint32_t)__shfl((int)bk.v, e);
+      if constexpr (KEYS) {
+        const uint32_t rk = same ? rv : (uint32_t)__shfl((int)bk.k, e);
+        load_raw<BF16>(kb + (uint64_t)rk * kRow, 0, col, k[u]);
+      }
+      load_raw<BF16>(vb + (uint64_t)rv * kRow, 0, col, v[u]);
+    }
+  };
+  auto consume = [&](const Block &bk, int q, const RowRaw<BF16> (&k)[KEYS ? U : 1],
+                     const RowRaw<BF16> (&v)[U]) {
+    float z[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      z[u] = __shfl(bk.z, kBatch * q + 4 * u + sub);
+      if constexpr (KEYS) {
+        float d = 0.f;
+        if constexpr (BF16) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t qw = st.qp[e], kw = k[u].v[0][e];
+            d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, qw),
+                                                __builtin_bit_cast(bf16x2, kw), d, false);
+          }
+        } else {
+          float kv[8];
+          unpack_raw<BF16>(k[u], kv);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) d = fmaf(st.q[e], kv[e], d);
+        }
+        z[u] += p.scale * row_sum16(d);
+      }
+    }
+    float w[U];
+    if constexpr (KEYS || SCORES) {
+      float mn = st.m;
+#pragma unroll
+      for (int u = 0; u < U; ++u) mn = fmaxf(mn, z[u]);
+      const float f = expf(st.m - mn);
+      st.m = mn;
+      st.l *= f;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) st.o[c] *= f;
+#pragma unroll
+      for (int u = 0; u < U; ++u) w[u] = expf(z[u] - mn);
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u) w[u] = z[u];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float vv[8];
+      unpack_raw<BF16>(v[u], vv);
+      st.l += w[u];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) st.o[c] = fmaf(w[u], vv[c], st.o[c]);
+    }
+  };
+  const int nb = (t1 - t0 + 63) >> 6;
+  Raw r1, r2;
+  Block cur, nxt;
+  RowRaw<BF16> ka[KEYS ? U : 1], va[U], kc[KEYS ? U : 1], vc[U];
+  fetch(0, r1);
+  fetch(1, r2);
+  resolve(r1, cur);
+  issue(cur, 0, ka, va);
+  for (int n = 0; n < nb; ++n) {
+    const int left = t1 - t0 - 64 * n;  // entries from this block on
+    r1 = r2;
+    fetch(n + 2, r2);
+    resolve(r1, nxt);
+#pragma unroll
+    for (int q = 0; q < kBatches; q += 2) {
+      issue(cur, q + 1, kc, vc);
+      consume(cur, q, ka, va);
+      if (left <= kBatch * (q + 1)) return;
+      if (q + 2 < kBatches) issue(cur, q + 2, ka, va);
+      else issue(nxt, 0, ka, va);
+      consume(cur, q + 1, kc, vc);
+      if (left <= kBatch * (q + 2)) return;
+    }
+    cur = nxt;
+  }
+}
+
+template <bool BF16, int MODE, int NT>
+__global__ __launch_bounds__(NT) void k_gather(Params p, Work w, const int32_t *idx, void *out,
+                                               int split, int fused) {
+  constexpr int NW = NT / 64;
+  __shared__ float red[NW][kHeadDim], red_m[NW], red_l[NW];
+  const int s = blockIdx.x;
+  const int row = fused ? ordered_row(w, (int)blockIdx.y, p.R) : (int)blockIdx.y;
+  const int b = row / p.R, r = row % p.R, g = r / p.G;
+  const int L = seq_len(p, b);
+  const int n_list = attend_list_len(p, b, L, fused);
+  const int nsp = (n_list + split - 1) / split;
+  const int tid = threadIdx.x, l = lane_id(), col = l & 15, sub = l >> 4, wv = wave_id();
+  const int64_t orow = (int64_t)b * p.Hq + r;
+  if (n_list == 0 || L == 0) {  // nothing kept: zero output
+    if (s == 0 && tid < kHeadDim) store_out<BF16>(out, orow * kHeadDim + tid, 0.f);
+    return;
+  }
+  if (s >= nsp) return;
+  const int e0 = s * split, n = (n_list - e0) < split ? (n_list - e0) : split;
+  const int64_t ist = fused && p.idx_stride > 0 ? p.idx_stride : p.k_max;
+  const int32_t *irow = idx + (int64_t)row * ist;
+  const float *wrow = p.weights ? p.weights + (int64_t)row * ist : nullptr;
+  const float *srow = w.sigma + (int64_t)row * p.k_max;
+
+  GatherAcc<BF16> st;
+  st.m = MODE == kGatherWeights ? 0.f : kLogitFloor;
+  st.l = 0.f;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) st.o[c] = 0.f;
+  if constexpr (MODE != kGatherWeights) {
+    RowRaw<BF16> qr;
+    load_raw<BF16>(p.q, orow * kHeadDim, col, qr);
+    if constexpr (BF16) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) st.qp[e] = qr.v[0][e];
+    } else {
+      unpack_raw<BF16>(qr, st.q);
+    }
+  }
+  // The wave's share, in whole batches of 16 entries.
+  const int per = ((n + NW - 1) / NW + 15) & ~15;
+  const int a = __builtin_amdgcn_readfirstlane(e0 + min(n, wv * per));
+  const int z = __builtin_amdgcn_readfirstlane(e0 + min(n, wv * per + per));
+  if constexpr (MODE == kGatherWeights) {
+    gather_entries<BF16, false, false>(p, b, g, L, irow, srow, nullptr, a, z, st);
+  } else if constexpr (MODE == kGatherKeys) {
+    gather_entries<BF16, true, false>(p, b, g, L, irow, nullptr, wrow, a, z, st);
+  } else {
+    const RowPlan rp = row_plan(p, b, L);
+    const int k0 = __builtin_amdgcn_readfirstlane(rp.ns);
+    const int k1 = __builtin_amdgcn_readfirstlane(rp.ns + rp.kh);
+    gather_entries<BF16, false, true>(p, b, g, L, irow, srow, nullptr, max(a, k0), min(z, k1), st);
+    gather_entries<BF16, true, false>(p, b, g, L, irow, nullptr, wrow, a, min(z, k0), st);
+    gather_entries<BF16, true, false>(p, b, g, L, irow, nullptr, wrow, max(a, k1), z, st);
+  }
+
+  // Over the four groups of a wave, then over the waves.
+  float m = fmaxf(st.m, __shfl_xor(st.m, 16));
+  m = fmaxf(m, __shfl_xor(m, 32));
+  const float f = MODE == kGatherWeights ? 1.f : expf(st.m - m);
+  float ls = st.l * f;
+  ls += __shfl_xor(ls, 16);
+  ls += __shfl_xor(ls, 32);
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    float v = st.o[c] * f;
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+    if (sub == 0) red[wv][8 * col + c] = v;
+  }
+  if (l == 0) {
+    red_m[wv] = m;
+    red_l[wv] = ls;
+  }
+  __syncthreads();
+  if (tid < kHeadDim) {
+    float M = red_m[0];
+#pragma unroll
+    for (int v = 1; v < NW; ++v) M = fmaxf(M, red_m[v]);
+    float o = 0.f, sum = 0.f;
+#pragma unroll
+    for (int v = 0; v < NW; ++v) {
+      const float fv = MODE == kGatherWeights ? 1.f : expf(red_m[v] - M);
+      o += fv * red[v][tid];
+      sum += fv * red_l[v];
+    }
+    if (nsp == 1) {
+      store_out<BF16>(out, orow * kHeadDim + tid, sum > 0.f ? o / sum : 0.f);
+    } else {
+      float *pp = w.part + (orow * w.nsplit + s) * kPartStride;
+      if (tid == 0) {
+        pp[0] = M;
+        pp[1] = sum;
+      }
+      pp[2 + tid] = o;
+    }
+  }
+}
+
 // Byte offsets of the dynamic LDS areas of k_attend (host and device agree):
-// per list entry its value row (and key row, when the logits are
-// recomputed) as 32-bit row indices, its weights, and its position where
-// entries can be skipped (recomputed logits) or are built (union).
+// per list entry its value row and key row as 32-bit row indices, its
+// weights, its position and (union) its heads.
 struct AttLds {
   int voff, koff, e, pos, hm, q, red, lred, total;
-  __host__ __device__ AttLds(int split, int nh, bool recompute, bool uni = false) {
+  __host__ __device__ AttLds(int split, int nh, bool uni = false) {
     const int nhb = nh < kAttHeads ? nh : kAttHeads;
     int o = 0;
     voff = o; o += 4 * split;
-    koff = o; o += recompute ? 4 * split : 0;
+    koff = o; o += 4 * split;
     e = o; o += 4 * nh * split;
-    pos = o; o += (recompute || uni) ? 4 * split : 0;
+    pos = o; o += 4 * split;
     hm = o; o += uni ? 4 * split : 0;
-    q = o; o += recompute ? 4 * nh * kHeadDim : 0;
+    q = o; o += 4 * nh * kHeadDim;
     red = o; o += 4 * kWaves * nhb * kHeadDim;
     lred = o; o += 4 * kWaves * nhb;
     total = o;
@@ -3026,34 +3293,32 @@ struct AttLds {
 // each over its own positions only.  HBU: heads accumulated per pass over
 // the value rows in group mode (4 for groups of at most 4 heads: fewer
 // registers, three waves per SIMD instead of two).
-template <bool BF16, bool FUSED, bool GRP, bool UNI = false, int HBU = kAttHeads>
+template <bool BF16, bool FUSED, bool UNI = false, int HBU = kAttHeads>
 __global__ __launch_bounds__(kBlock) void k_attend(Params p, Work w, const int32_t *idx, void *out,
                                                    int split) {
-  static_assert(!UNI || (BF16 && FUSED && GRP), "union attention: fused bf16 group rows");
+  static_assert(!UNI || (BF16 && FUSED), "union attention: fused bf16 group rows");
   extern __shared__ int64_t att_dyn[];
   __shared__ float mh[kMaxGroup];
   __shared__ float hmax[kWaves][kMaxGroup];
-  constexpr int U = (BF16 && !GRP) ? 8 : 4;  // positions per 16-lane group per step
-  constexpr int HB = GRP ? HBU : 1;  // heads accumulated per pass
+  constexpr int U = 4;     // positions per 16-lane group per step
+  constexpr int HB = HBU;  // heads accumulated per pass
 
   const int rows_per_b = UNI ? p.Hkv : p.R;  // union rows are the groups
   const int s = blockIdx.x, row = FUSED ? ordered_row(w, (int)blockIdx.y, rows_per_b)
                                         : (int)blockIdx.y;
   const int b = row / rows_per_b, r = row % rows_per_b;
-  constexpr bool grp = GRP;
-  const int nh = grp ? p.G : 1;
+  const int nh = p.G;
   const int nhb = nh < kAttHeads ? nh : kAttHeads;
-  const int h0 = grp ? r * p.G : r;
-  const int g = grp ? r : r / p.G;
+  const int h0 = r * p.G;
+  const int g = r;
   const int L = seq_len(p, b);
   const int n_list = UNI ? L : attend_list_len(p, b, L, FUSED);
   const int nsp = (n_list + split - 1) / split;
   const int tid = threadIdx.x, l = lane_id(), col = l & 15, sub = l >> 4, wv = wave_id();
-  const bool recompute = UNI || attend_recompute(FUSED, p);
-  const AttLds lay(split, nh, recompute, UNI);
+  const AttLds lay(split, nh, UNI);
   char *dyn = (char *)att_dyn;
   uint32_t *voff_l = (uint32_t *)(dyn + lay.voff);  // value rows (kv_row)
-  uint32_t *koff_l = (uint32_t *)(dyn + lay.koff);  // key rows (recompute)
+  uint32_t *koff_l = (uint32_t *)(dyn + lay.koff);  // key rows
   float *e_l = (float *)(dyn + lay.e);
   int32_t *pos_l = (int32_t *)(dyn + lay.pos);
   uint32_t *hm_l = (uint32_t *)(dyn + lay.hm);  // UNI: each entry's head bits
@@ -3150,13 +3415,13 @@ __global__ __launch_bounds__(kBlock) void k_attend(Params p, Work w, const int32
     for (int t = tid; t < n; t += kBlock) {
       int32_t j = irow[t];
       if (j < 0 || j >= L) j = -1;
-      if (recompute) pos_l[t] = j;  // (fused lists hold only valid entries)
+      pos_l[t] = j;
       const int64_t jc = j >= 0 ? j : 0;
       voff_l[t] = kv_row(p.V, b, jc);
-      if (recompute) koff_l[t] = kv_row(p.K, b, jc);
+      koff_l[t] = kv_row(p.K, b, jc);
     }
   }
-  if (recompute && !BF16) {  // float32 queries for the vector-ALU logits
+  if (!BF16) {  // float32 queries for the vector-ALU logits
     for (int e = tid; e < nh * kHeadDim; e += kBlock) {
       const int64_t qo = ((int64_t)b * p.Hq + h0 + e / kHeadDim) * kHeadDim + e % kHeadDim;
       q_l[e] = ((const float *)p.q)[qo];
@@ -3165,13 +3430,7 @@ __global__ __launch_bounds__(kBlock) void k_attend(Params p, Work w, const int32
   __syncthreads();
 
   // Logits z[h][t] = scale * q_h . K_j (kept in e_l until the max is known).
-  // Per-head fused rows arrive with their softmax weights already formed
-  // (relative to the row's maximum, so all splits share one reference).
-  if (!recompute) {
-    const float *wrow = w.sigma + (int64_t)row * p.k_max + e0;
-    for (int t = tid; t < n; t += kBlock) e_l[t] = wrow[t];
-    if (tid == 0) mh[0] = 0.f;
-  } else if constexpr (BF16) {
+  if constexpr (BF16) {
     // Logits by MFMA: a wave scores 16 kept positions per tile, each lane
     // loading its position's key slices straight into the operand layout;
     // the query operand's rows are the nh heads served.  Two tiles' loads
@@ -3230,7 +3489,7 @@ __global__ __launch_bounds__(kBlock) void k_attend(Params p, Work w, const int32
     }
   }
   __syncthreads();
-  if (recompute) {
+  {
     // Per-head maxima: every wave reduces its share, one barrier, then
     // thread h combines the waves.  With per-entry weights omega the logit
     // becomes z + log(omega), so that exp(z' - m) = omega * exp(z - m) and
@@ -3460,8 +3719,9 @@ size_t select_lds_bytes(int nchunk, int lds_cap) {
   return (size_t)(2 * nchunk + 1) * 4 + (size_t)lds_cap * 4;
 }
 
-bool select_wide(const Params &p, size_t lds_bytes) {
-  return (size_t)(p.B * p.R) < (size_t)kSelectWideRows || lds_bytes > kSelectShareLds;
+bool select_wide(const Params &p, size_t lds_bytes, int64_t cands) {
+  return (size_t)(p.B * p.R) < (size_t)kSelectWideRows || lds_bytes > kSelectShareLds ||
+         cands > kBlock * reg_select_slots<kBlock>();
 }
 
 size_t select_lds_budget(bool wide) {
@@ -3469,6 +3729,12 @@ size_t select_lds_budget(bool wide) {
   // bucket scratch: about 9.9 KB at 256 threads, 14.1 KB at 1024) under the
   // 160 KB of a workgroup.
   return wide ? 144 * 1024 : 150 * 1024;
+}
+
+// Whether the attention takes the selection's scores: per-head rows on exact
+// scores (label scores are not logits; group rows need each head's own).
+static bool uses_sigma(const Params &p, const Work &w) {
+  return !p.group_shared && !p.labels && w.union_chunk == 0;
 }
 
 // Rows of at most 4K scores fit the registers of 256 threads; with two or
@@ -3487,9 +3753,7 @@ hipError_t launch_select_candidates(const Params &p, const Work &w, int32_t *idx
                                     bool wide, hipStream_t st) {
   const size_t lds = select_lds_bytes(w.nchunk, lds_cap);
   const unsigned rows = (unsigned)(p.B * p.R);
-  // The kept scores / weights only serve an attention that does not
-  // recompute its logits.
-  float *vals = attend_recompute(true, p) ? nullptr : w.sigma;
+  float *vals = uses_sigma(p, w) ? w.sigma : nullptr;
   if (w.force_repair) {
     const size_t rlds = row_select_lds(p.ncap);
     if (row_narrow(rows, p.ncap))
@@ -3542,7 +3806,7 @@ hipError_t launch_dense_select(const Params &p, const Work &w, int32_t *idx, hip
   k_dsel_hist<2><<<grid, kBlock, 0, st>>>(p, w);
   k_dsel_digit<2><<<rows, kBlock, 0, st>>>(p, w);
   k_dsel_count<<<grid, kBlock, 0, st>>>(p, w);
-  k_dsel_write<<<grid, kBlock, 0, st>>>(p, w, idx, attend_recompute(true, p) ? nullptr : w.sigma);
+  k_dsel_write<<<grid, kBlock, 0, st>>>(p, w, idx, uses_sigma(p, w) ? w.sigma : nullptr);
   return hipGetLastError();
 }
 
@@ -3585,41 +3849,37 @@ hipError_t launch_repair(const Params &p, const Work &w, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Workgroups to aim for when rows are split.  Fused calls: two per CU; with
-// 1024, few rows were cut into pieces short enough for their latency chains
-// and the merge to dominate (1M-key group-shared batch of 8 rows: attention
-// 36 -> 30 us at 512; Table 2's label shape at batch 1 and 4, 2-5% faster).
-// Unfused calls (the weighted backend over caller lists, key and value rows
-// per entry) keep four per CU: their low-sparsity lists are bandwidth-bound,
-// and at 512 Table 1's batch 1 took 0.281 instead of 0.177 ms at 2x.
+// Group rows: workgroups to aim for when rows are split.  Fused calls: two
+// per CU; with 1024, few rows were cut into pieces short enough for their
+// latency chains and the merge to dominate (1M-key group-shared batch of 8
+// rows: attention 36 -> 30 us at 512).  Unfused calls (caller lists) keep four
+// per CU: their low-sparsity lists are bandwidth-bound.
 constexpr int kAttendWorkgroupsFused = 512;
 constexpr int kAttendWorkgroups = 1024;
 constexpr int kAttendLdsMax = 60 * 1024;  // dynamic LDS of one attend workgroup
 constexpr int kAttendMinEntries = 64;     // fewest list entries worth a workgroup of their own
 constexpr int kAttendRowsWhole = 256;     // this many rows fill the chip unsplit
 
-// Positions per attend workgroup: a row is not split when there are enough
-// rows to give every CU a workgroup and the whole list fits one workgroup's
-// LDS (a split then costs the merge launch, more than the extra parallelism
-// saves); otherwise rows are split into about kAttendWorkgroupsFused
-// (fused) or kAttendWorkgroups (unfused) workgroups
+// Positions per attend workgroup of group rows: a row is not split when there
+// are enough rows to give every CU a workgroup and the whole list fits one
+// workgroup's LDS (a split then costs the merge launch, more than the extra
+// parallelism saves); otherwise rows are split into about
+// kAttendWorkgroupsFused (fused) or kAttendWorkgroups (unfused) workgroups
 // in all, at least 64 positions each, within the LDS budget.
 int attend_split(const Params &p, int k_max_positions, bool fused) {
   const int64_t rows = (int64_t)p.B * p.R;
   const int64_t k_max = k_max_positions > 0 ? k_max_positions : 1;
-  const int nh = p.group_shared ? p.G : 1;
-  const bool rc = attend_recompute(fused, p);
   const int64_t target = fused ? kAttendWorkgroupsFused : kAttendWorkgroups;
   int64_t nsplit = (target + rows - 1) / rows;
   if (rows >= kAttendRowsWhole && k_max <= 4096 &&  // (bounded: the LDS sum stays in int)
-      AttLds((int)((k_max + 63) / 64 * 64), nh, rc).total <= kAttendLdsMax)
+      AttLds((int)((k_max + 63) / 64 * 64), p.G).total <= kAttendLdsMax)
     nsplit = 1;
   const int64_t most = (k_max + kAttendMinEntries - 1) / kAttendMinEntries;
   if (nsplit > most) nsplit = most;
   if (nsplit < 1) nsplit = 1;
   int64_t split = (k_max + nsplit - 1) / nsplit;
   split = (split + 63) / 64 * 64;
-  while (split > 64 && AttLds((int)split, nh, rc).total > kAttendLdsMax) split -= 64;
+  while (split > 64 && AttLds((int)split, p.G).total > kAttendLdsMax) split -= 64;
   // As many splits as that takes, the entries spread evenly over them (no
   // smaller than the LDS-capped size, so still within the budget).
   nsplit = (k_max + split - 1) / split;
@@ -3627,17 +3887,71 @@ int attend_split(const Params &p, int k_max_positions, bool fused) {
   return (int)split;
 }
 
+// Per-head rows: threads per workgroup and entries per workgroup.  About
+// kGatherWaves waves in all (16 per CU), each with at least 64 entries; a row
+// of up to 16 waves is one workgroup and needs no merge (a launch of 4-5 us),
+// and so does a row that one workgroup gathers in that time anyway
+// (kGatherWhole bytes).
+constexpr int kGatherWaves = 4096;
+constexpr int64_t kGatherWhole = 420 * 1024;
+struct GatherPlan {
+  int nt, split, nsplit;
+};
+static GatherPlan gather_plan(int64_t rows, int64_t k, int entry_bytes) {
+  k = k > 0 ? k : 1;
+  int64_t waves = (kGatherWaves + rows - 1) / rows;
+  const int64_t blocks = (k + 63) / 64;
+  waves = waves < blocks ? waves : blocks;
+  if (waves > 16 && k * entry_bytes <= kGatherWhole) waves = 16;
+  GatherPlan pl;
+  pl.nt = waves <= 4 ? 256 : (waves <= 8 ? 512 : 1024);
+  pl.nsplit = (int)((waves + 15) / 16);
+  const int64_t split = ((k + pl.nsplit - 1) / pl.nsplit + 63) / 64 * 64;
+  pl.split = (int)split;
+  pl.nsplit = (int)((k + split - 1) / split);
+  return pl;
+}
+
 int attend_nsplit(const Params &p) {
-  // The larger of the fused and unfused split counts (the unfused layout
-  // needs more LDS per entry, hence smaller splits).
+  // The largest split count of any call of this shape.
+  const int64_t k_max = p.k_max > 0 ? p.k_max : 1;
+  if (!p.group_shared) return gather_plan((int64_t)p.B * p.R, k_max, 1 << 20).nsplit;
   int most = 1;
   for (int fused = 0; fused < 2; ++fused) {
     const int split = attend_split(p, p.k_max, fused != 0);
-    const int64_t k_max = p.k_max > 0 ? p.k_max : 1;
     const int ns = (int)((k_max + split - 1) / split);
     most = ns > most ? ns : most;
   }
   return most;
+}
+
+template <bool BF16, int MODE>
+static void launch_gather_nt(const Params &p, const Work &w, const int32_t *idx, void *out,
+                             const GatherPlan &pl, bool fused, hipStream_t st) {
+  const dim3 grid(pl.nsplit, p.B * p.R);
+  const int f = fused ? 1 : 0;
+  if (pl.nt == 256) k_gather<BF16, MODE, 256><<<grid, 256, 0, st>>>(p, w, idx, out, pl.split, f);
+  else if (pl.nt == 512) k_gather<BF16, MODE, 512><<<grid, 512, 0, st>>>(p, w, idx, out, pl.split, f);
+  else k_gather<BF16, MODE, 1024><<<grid, 1024, 0, st>>>(p, w, idx, out, pl.split, f);
+}
+
+template <bool BF16>
+static hipError_t launch_gather(const Params &p, const Work &w, const int32_t *idx, void *out,
+                                bool fused, hipStream_t st) {
+  const bool keys = !fused || p.labels;
+  const bool scores = !keys && (p.n_sink + p.n_local > 0 || p.idx_stride > 0);
+  const int64_t list = fused && p.idx_stride > 0 ? p.idx_stride : p.k_max;
+  const int row_bytes = kHeadDim * (BF16 ? 2 : 4);
+  const GatherPlan pl = gather_plan((int64_t)p.B * p.R, list, keys ? 2 * row_bytes : row_bytes);
+  if (keys) launch_gather_nt<BF16, kGatherKeys>(p, w, idx, out, pl, fused, st);
+  else if (scores) launch_gather_nt<BF16, kGatherScores>(p, w, idx, out, pl, fused, st);
+  else launch_gather_nt<BF16, kGatherWeights>(p, w, idx, out, pl, fused, st);
+  if (pl.nsplit > 1) {
+    const unsigned rows = (unsigned)(p.B * p.Hq);
+    if (fused) k_merge<BF16, true><<<rows, kMergeThreads, 0, st>>>(p, w, out, pl.split);
+    else k_merge<BF16, false><<<rows, kMergeThreads, 0, st>>>(p, w, out, pl.split);
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_sample_rest(const Params &p, int32_t *list, const uint32_t *draws, int s,
@@ -3649,7 +3963,7 @@ hipError_t launch_sample_rest(const Params &p, int32_t *list, const uint32_t *dr
 
 int union_chunk(const Params &p) {
   int c = kUnionChunkMax;
-  while (c > 64 && AttLds(c, p.G, true, true).total > kAttendLdsMax) c -= 64;
+  while (c > 64 && AttLds(c, p.G, true).total > kAttendLdsMax) c -= 64;
   return c;
 }
 
@@ -3659,37 +3973,28 @@ hipError_t launch_attend(const Params &p, const Work &w, const int32_t *idx, voi
     if (!p.bf16 || p.group_shared || w.union_chunk > kUnionChunkMax || !w.ustart)
       return hipErrorInvalidValue;
     const int split = w.union_chunk;
-    const size_t lds = (size_t)AttLds(split, p.G, true, true).total;
+    const size_t lds = (size_t)AttLds(split, p.G, true).total;
     const int nsplit = (int)((p.ncap + split - 1) / split);
     const dim3 grid(nsplit, p.B * p.Hkv);
-    if (p.G <= 4) k_attend<true, true, true, true, 4><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
-    else k_attend<true, true, true, true><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
+    if (p.G <= 4) k_attend<true, true, true, 4><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
+    else k_attend<true, true, true><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
     if (nsplit > 1) k_merge<true, true><<<(unsigned)(p.B * p.Hq), kMergeThreads, 0, st>>>(p, w, out, split);
     return hipGetLastError();
   }
+  if (!p.group_shared)
+    return p.bf16 ? launch_gather<true>(p, w, idx, out, fused, st)
+                  : launch_gather<false>(p, w, idx, out, fused, st);
   const int split = attend_split(p, p.k_max, fused);
-  const size_t lds = (size_t)AttLds(split, p.group_shared ? p.G : 1,
-                                    attend_recompute(fused, p)).total;
+  const size_t lds = (size_t)AttLds(split, p.G).total;
   const int64_t kk = p.k_max > 0 ? p.k_max : 1;
   const int nsplit = (int)((kk + split - 1) / split);
   const dim3 grid(nsplit, p.B * p.R);
-  const bool g = p.group_shared != 0;
   if (p.bf16) {
-    if (fused) {
-      if (g) k_attend<true, true, true><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
-      else k_attend<true, true, false><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
-    } else {
-      if (g) k_attend<true, false, true><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
-      else k_attend<true, false, false><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
-    }
+    if (fused) k_attend<true, true><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
+    else k_attend<true, false><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
   } else {
-    if (fused) {
-      if (g) k_attend<false, true, true><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
-      else k_attend<false, true, false><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
-    } else {
-      if (g) k_attend<false, false, true><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
-      else k_attend<false, false, false><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
-    }
+    if (fused) k_attend<false, true><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
+    else k_attend<false, false><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
   }
   if (nsplit > 1) {
     const unsigned rows = (unsigned)(p.B * p.Hq);

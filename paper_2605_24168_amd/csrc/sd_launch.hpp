@@ -18,10 +18,13 @@ hipError_t launch_score_stream(const Params &p, const Work &w, hipStream_t st,
                                hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 size_t select_lds_bytes(int nchunk, int lds_cap);
 // Whether the candidate selection runs 1024-thread workgroups: when the rows
-// are too few to fill the GPU one workgroup each, or when a workgroup's LDS
+// are too few to fill the GPU one workgroup each; when a workgroup's LDS
 // (lds_bytes, at the 256-thread budget) leaves room for no second one on a
-// compute unit, so that more loads are in flight per compute unit.
-bool select_wide(const Params &p, size_t lds_bytes);
+// compute unit, so that more loads are in flight per compute unit; or when a
+// row's candidates (cands: about one deviation above what is expected) are
+// more than the registers of 256 threads hold (128K label rows at 20x, 10K
+// candidates each: 65 us through LDS copies, 21 us in registers).
+bool select_wide(const Params &p, size_t lds_bytes, int64_t cands);
 // Dynamic LDS available to the candidate selection at that width.
 size_t select_lds_budget(bool wide);
 // Whether one workgroup selects the top k of a full row of n scores in one

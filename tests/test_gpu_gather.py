@@ -1,0 +1,90 @@
+"""Gather-attention of per-head rows at the sizes where a wave's share, a
+block of 64 indices or a row's workgroups change: lists of one entry up to
+several blocks per wave, rows split over workgroups, caller lists with
+skipped entries, key and value caches on different page tables, and fused
+calls whose softmax joins the selection's scores with recomputed logits.
+"""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2605_24168_amd import synth
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sd():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2605_24168_amd import sparse_decode
+    sparse_decode.set_debug(0)
+    return sparse_decode
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("layout", ["bhnd", "paged"])
+@pytest.mark.parametrize("B,Hq,k", [
+    (1, 2, 1), (1, 2, 15), (1, 2, 17), (1, 2, 65), (2, 4, 257),  # 1-5 waves
+    (1, 2, 1040), (1, 2, 4999),                                  # one workgroup; several
+    (24, 12, 300), (70, 16, 130),                                # few waves per row
+])
+def test_weighted_lists(sd, dtype, layout, B, Hq, k):
+    lens = [5000 - 37 * b for b in range(B)]
+    inp = synth.make_inputs(2, seed=7, seq_lens=lens, Hq=Hq, Hkv=2, dtype=dtype, layout=layout,
+                            ncap=5008)
+    idx = synth.index_sets(inp, k, seed=3, k_max=k + 3, extra_invalid=min(2, k - 1))
+    w = synth.index_weights(idx.shape, seed=3, zero_frac=0.1)
+    q, cache, sl = sd.cache_from_inputs(inp)
+    sp = sd.Sparsity(ratio=1.0)
+    out = sd.sparse_decode_attend_weighted(q, cache, sl, torch.from_numpy(idx).cuda(),
+                                           torch.from_numpy(w).cuda(), sp)
+    if layout == "paged":  # values on a page table of their own
+        perm = np.random.default_rng(1).permutation(inp.num_pages).astype(np.int64)
+        back = np.argsort(perm)
+        vt = np.where(inp.block_table >= 0, back[np.maximum(inp.block_table, 0)], -1).astype(np.int32)
+        moved = cache.v[torch.from_numpy(perm).cuda()].contiguous()
+        ck, cv = cache.c("k"), cache.c("v")
+        table = torch.from_numpy(vt).cuda()
+        cv.t.data, cv.block_table = moved.data_ptr(), table.data_ptr()
+        out2 = torch.empty_like(out)
+        ti, tw = torch.from_numpy(idx).cuda(), torch.from_numpy(w).cuda()
+        st = sd.lib.sparse_decode_attend_weighted(
+            C.byref(sd._tensor(q, "q")), C.byref(ck), C.byref(cv), sl.data_ptr(),
+            C.byref(sd._tensor(ti, "idx")), C.byref(sd._tensor(tw, "w")), C.byref(sp.c()),
+            C.byref(sd._tensor(out2, "out")), sd._stream(None))
+        assert st == 0
+        torch.cuda.synchronize()
+        assert torch.equal(out, out2)
+    torch.cuda.synchronize()
+    usable = (idx >= 0) & (idx < inp.seq_lens[:, None, None]) & (w > 0)
+    kk = int(usable.sum(-1).max()) or 1
+    oi = np.full(idx.shape[:2] + (kk,), -1, np.int32)
+    ow = np.zeros(oi.shape, np.float32)
+    for b in range(B):
+        for r in range(Hq):
+            u = usable[b, r]
+            oi[b, r, :u.sum()], ow[b, r, :u.sum()] = idx[b, r, u], w[b, r, u]
+    ref = O.attend_weighted(inp, oi, ow)
+    ref = ref[0] if isinstance(ref, tuple) else ref
+    ok, ratio, _ = P.out_errors(P.to_host(out), ref, dtype)
+    assert ok, ratio
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n_sink,n_local,ratio", [(1, 0, 50.0), (0, 33, 20.0), (128, 128, 9.0),
+                                                  (40, 500, 300.0)])
+def test_forced_windows_join_the_scores(sd, dtype, n_sink, n_local, ratio):
+    inp = synth.make_inputs(2, seed=9, seq_lens=[6000, 200, 64, 1, 0], ncap=6001, Hq=8, Hkv=4,
+                            dtype=dtype, ratio=ratio, n_sink=n_sink, n_local=n_local)
+    q, cache, lens = sd.cache_from_inputs(inp)
+    out, idx = sd.sparse_decode_attention(q, cache, lens, sd.sparsity_from_inputs(inp),
+                                          k_max=O.k_max_for(inp))
+    torch.cuda.synchronize()
+    ref = O.attend(inp, idx.cpu().numpy())[0]
+    ok, worst, _ = P.out_errors(P.to_host(out), ref, dtype)
+    assert ok, worst
