@@ -316,7 +316,9 @@ sd_status sparse_decode_profile_mean(sd_profile *out, int32_t *n_calls);
  * overriding the cost rule; flags & 16 / & 32 turn the candidate selection
  * over several workgroups per row off / on wherever it applies (calls with
  * fewer than 256 rows, no group-deduplicated attention), overriding its
- * cost rule (rows expecting 8K candidates or more).  0 restores normal. */
+ * cost rule (rows expecting 8K candidates or more); flags & 64, and 16 and
+ * 32 too, keep calls on the candidate path whose rows the cost rule for
+ * short contexts would select from their full scores.  0 restores normal. */
 sd_status sparse_decode_set_debug(int32_t flags);
 
 /* Measurement helper, not a step of the method: one streaming read of

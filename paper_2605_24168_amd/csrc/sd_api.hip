@@ -334,6 +334,26 @@ bool all_rows_fall_back(const Shape &s, const sd_sparsity *sp, int wave_keys, in
   return 2 * (r - 1) * span > cap * m;
 }
 
+// Whether a call is faster with every row selected from its full scores
+// (three kernels: scores, selection, attention) than with sampled thresholds
+// and candidates (six).  The candidate path's launches and the latency of its
+// short kernels cost about 18 us (labels: 14 us) more whatever the size, and
+// 5 us more per 128 groups sampled; full scores cost 1.2 us more per million
+// scores, written and read back (labels 1.45), 8 us per 64K scores of a row
+// (one workgroup reads it), and 9 us per GB of keys (labels 35), their stream
+// being the slower one.  Least squares over 434 (labels 382) shapes measured
+// both ways: 1-32 sequences of 4K-128K keys, 1-32 KV heads, both layouts, at
+// 20x; 5 us (labels 3) are kept as a margin.  At the sides: 32 heads on 8 KV
+// heads, paged, 8K keys: 68 against 28 us for one sequence, 111 against 95
+// for 16; 64K keys: 75 against 68 us for one, 153 against 164 for 4.
+bool full_scores_pay(const Shape &s, bool labels) {
+  const double scores = 1e-6 * s.B * s.R * (double)s.ncap;
+  const double key_gb = 256e-9 * s.B * s.Hkv * (double)s.ncap;
+  const double len = (double)s.ncap / 65536.0;
+  if (labels) return 1.45 * scores + 7.0 * len + 35.0 * key_gb < 11.0;
+  return 1.2 * scores + 8.0 * len + 9.0 * key_gb - 5.0 * (s.B * s.Hkv / 128.0) < 13.0;
+}
+
 Layout layout_for(const Shape &s, int64_t k_max, bool fused, const sd_sparsity *sp,
                   bool labels = false, bool allow_union = true) {
   Layout L{};
@@ -786,19 +806,18 @@ sd_status attention_impl(const sd_tensor *q, const sd_kv *K, const sd_kv *V,
   // tens of thousands of candidates in one workgroup per row costs more than
   // selecting full rows over 16 or more workgroups each.
   if (L.dsel_parts >= 16 && cands >= kManyCandidates) w.force_repair = 1;
+  const sd::RowPlan full_plan =
+      sd::row_plan((int)std::min<int64_t>(s.ncap, INT32_MAX), sp->n_sink, sp->n_local,
+                   sp->k_override ? k_max : sd::budget_rule(s.ncap, sp->ratio, sp->k_rounding),
+                   (int)k_max);
+  const bool one_pass = sd::row_selects(full_plan.hi - full_plan.lo, full_plan.kh);
+  if (one_pass && !(g_debug.load() & (16 | 32 | 64)) && full_scores_pay(s, labels != nullptr))
+    w.force_repair = 1;
   // Those rows select over several workgroups each when they are few and
   // one workgroup would need several passes over a row (one pass by one
   // workgroup takes 15-25 us at 32K-128K scores; the pieces' eight kernels
   // more than that whatever the row).
-  if (w.force_repair && L.dsel_parts) {
-    const sd::RowPlan rp = sd::row_plan((int)std::min<int64_t>(s.ncap, INT32_MAX), sp->n_sink,
-                                        sp->n_local,
-                                        sp->k_override ? k_max
-                                                       : sd::budget_rule(s.ncap, sp->ratio,
-                                                                         sp->k_rounding),
-                                        (int)k_max);
-    if (!sd::row_selects(rp.hi - rp.lo, rp.kh)) w.dsel_parts = L.dsel_parts;
-  }
+  if (w.force_repair && !one_pass) w.dsel_parts = L.dsel_parts;
   sd::Params p = make_params(q, K, V, seq_lens, sp, s, k_max);
   if (labels) {
     p.labels = (const uint16_t *)labels->t.data;

@@ -1,0 +1,84 @@
+"""Short contexts: calls whose rows the cost rule selects from full scores
+(scores, selection, attention) give, bit for bit, the lists and outputs of the
+candidate path (debug flag 64 keeps a call on it), for every kind of fused
+call, both layouts, ragged batches with empty sequences, capacities beyond
+the sequences and budgets set per sequence.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2605_24168_amd import synth
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+CANDIDATES = 64
+
+
+@pytest.fixture(scope="module")
+def sd():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2605_24168_amd import sparse_decode
+    sparse_decode.set_debug(0)
+    return sparse_decode
+
+
+def both(sd, call):
+    """(outputs, rows selected from full scores) by the rule and without it."""
+    got = []
+    for flags in (0, CANDIDATES):
+        sd.set_debug(flags)
+        sd.set_profiling(True)
+        try:
+            out = [P.to_host(t) for t in call()]
+            torch.cuda.synchronize()
+            got.append((out, sd.last_profile()["repaired_rows"]))
+        finally:
+            sd.set_profiling(False)
+            sd.set_debug(0)
+    return got
+
+
+@pytest.mark.parametrize("kind", ["exact", "shared", "forced", "override", "label", "sampled",
+                                  "noalloc"])
+@pytest.mark.parametrize("layout", ["bhnd", "paged"])
+@pytest.mark.parametrize("Hq,Hkv,lens,ncap", [
+    (8, 8, [2049, 4096], 4097),            # one row per group
+    (32, 8, [8191], 8192),                 # registers hold the rows
+    (10, 2, [17003, 0, 1, 9000], 20000),   # 5 heads per group; rows past the registers
+    (16, 1, [3000, 64, 65], 30000),        # 16 heads; mostly empty capacity
+])
+def test_short_context_rule(sd, kind, layout, Hq, Hkv, lens, ncap):
+    inp = synth.make_inputs(2, seed=11, seq_lens=lens, ncap=ncap, Hq=Hq, Hkv=Hkv, layout=layout,
+                            ratio=20.0, group_shared=kind == "shared",
+                            n_sink=70 if kind == "forced" else 0,
+                            n_local=33 if kind == "forced" else 0)
+    q, cache, sl = sd.cache_from_inputs(inp)
+    sp = sd.sparsity_from_inputs(inp)
+    kmax = O.k_max_for(inp)
+    if kind == "override":
+        sp.k_override = torch.tensor([min(kmax, 5 + 97 * b) for b in range(inp.B)],
+                                     dtype=torch.int32, device="cuda")
+    if kind == "label":
+        ch = synth.label_channels(Hkv)
+        lab = synth.label_cache_device_layout(inp, synth.label_cache(inp, ch))
+        labels = sd.Labels(t=torch.from_numpy(lab).view(torch.bfloat16).cuda(),
+                           channels=torch.from_numpy(ch).cuda())
+        call = lambda: sd.sparse_decode_label_attention(q, cache, labels, sl, sp, k_max=kmax)
+    elif kind == "sampled":
+        draws = torch.randint(-2**31, 2**31, (inp.B, Hq, 50), device="cuda").to(torch.int32)
+        call = lambda: sd.sparse_decode_sampled_attention(q, cache, sl, sp, draws, k_max=kmax)
+    elif kind == "noalloc":
+        call = lambda: sd.sparse_decode_attention_noalloc(
+            q, cache, sl, sp, torch.empty_like(q),
+            torch.empty((inp.B, Hq, kmax), dtype=torch.int32, device="cuda"))
+    else:
+        call = lambda: sd.sparse_decode_attention(q, cache, sl, sp, k_max=kmax)
+    (a, full), (b, cand) = both(sd, call)
+    for x, y in zip(a, b):
+        np.testing.assert_array_equal(x, y)
+    if kind != "noalloc":  # (its calls are not profiled)
+        assert full > 0 and cand < full, (full, cand)
