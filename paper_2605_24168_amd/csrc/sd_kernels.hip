@@ -165,21 +165,16 @@ constexpr int kPilotMinRank = 48;  // fewest sample ranks above the threshold
 
 // Of the m items in LDS (m <= the threads of the block), the krem-th
 // largest: the thread holding it stores it in sh->digit and the number of
-// items above it in sh->above (equal items agree).  Eight reads in flight:
-// one at a time is an LDS round trip per item (m = 200: 8 us).
+// items above it in sh->above (equal items agree).
 __device__ __forceinline__ void rank_items(const uint32_t *items, int m, int krem, SelShared *sh) {
   if ((int)threadIdx.x >= m) return;
   const uint32_t x = items[threadIdx.x];
   int gt = 0, ge = 0;
-  for (int y0 = 0; y0 < m; y0 += 8) {
-    uint32_t v[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = items[y0 + e < m ? y0 + e : m - 1];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      gt += y0 + e < m && v[e] > x ? 1 : 0;
-      ge += y0 + e < m && v[e] >= x ? 1 : 0;
-    }
+#pragma unroll 8
+  for (int y = 0; y < m; ++y) {
+    const uint32_t v = items[y];
+    gt += v > x ? 1 : 0;
+    ge += v >= x ? 1 : 0;
   }
   if (gt < krem && krem <= ge) {
     sh->digit = x;
@@ -1637,38 +1632,34 @@ __device__ __forceinline__ void reg_emit(const uint32_t (&key)[UMAX], const RegS
   const int lane = lane_id();
   const auto lst = uniform_ptr(irow);
   const auto val = uniform_ptr(vrow);
-  auto emit = [&](auto vals, auto wts, auto tie) {
-    int eq_run = eq_b, sel_run = sel0;
-    unroll_slots<UMAX>(sh.U, [&](auto uc) {
-      constexpr int u = decltype(uc)::value;
-      const int i = sh.i0 + 64 * u + lane;
-      const bool valid = !CHECK || i < sh.i1;
-      const uint32_t x = fresh(key[u]);
-      bool kept = valid && x > T;
-      if constexpr (decltype(tie)::value) {
-        const uint64_t eqm = __ballot(valid && x == T);
-        kept = kept || (valid && x == T && eq_run + lanes_below(eqm) < need_eq);
-        eq_run += __popcll(eqm);
+  // (one copy of the code with scalar flags: a copy per combination made the
+  // selection kernels five times as large, and code is fetched from memory
+  // again by every launch that follows a key stream)
+  const bool tie = __builtin_amdgcn_readfirstlane(ties ? 1 : 0) != 0;
+  const int form = __builtin_amdgcn_readfirstlane(!vrow ? 0 : (weights ? 2 : 1));
+  int eq_run = eq_b, sel_run = sel0;
+  unroll_slots<UMAX>(sh.U, [&](auto uc) {
+    constexpr int u = decltype(uc)::value;
+    const int i = sh.i0 + 64 * u + lane;
+    const bool valid = !CHECK || i < sh.i1;
+    const uint32_t x = fresh(key[u]);
+    bool kept = valid && x > T;
+    if (tie) {
+      const uint64_t eqm = __ballot(valid && x == T);
+      kept = kept || (valid && x == T && eq_run + lanes_below(eqm) < need_eq);
+      eq_run += __popcll(eqm);
+    }
+    const uint64_t km = __ballot(kept);
+    const int s = sel_run + lanes_below(km);
+    if (kept && s < k) {
+      lst[s] = (int32_t)pos(i);
+      if (form) {
+        const float v = key2f(x);
+        val[s] = form == 2 ? kept_weight(v, vmax, c2) : v;
       }
-      const uint64_t km = __ballot(kept);
-      const int s = sel_run + lanes_below(km);
-      if (kept && s < k) {
-        lst[s] = (int32_t)pos(i);
-        if constexpr (decltype(vals)::value) {
-          const float v = key2f(x);
-          val[s] = decltype(wts)::value ? kept_weight(v, vmax, c2) : v;
-        }
-      }
-      sel_run += __popcll(km);
-    });
-  };
-  auto emit_ties = [&](auto vals, auto wts) {
-    if (ties) emit(vals, wts, std::true_type{});
-    else emit(vals, wts, std::false_type{});
-  };
-  if (!vrow) emit_ties(std::false_type{}, std::false_type{});
-  else if (weights) emit_ties(std::true_type{}, std::true_type{});
-  else emit_ties(std::true_type{}, std::false_type{});
+    }
+    sel_run += __popcll(km);
+  });
 }
 
 // Candidate selection of a row by one workgroup, the keys held in registers
@@ -2243,7 +2234,13 @@ __device__ __forceinline__ void piece_hist(const Params &p, const Work &w, int r
     load_keys(base, key);
     count(base, key);
   }
-  mx = wave_max_u32(mx);
+  // (by shuffles: with the maximum in a scalar register the launch measured
+  // 1.2 us longer)
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const uint32_t t = (uint32_t)__shfl_xor((int)mx, o);
+    mx = t > mx ? t : mx;
+  }
   if (lane_id() == 0) atomicMax(&sh.kmax, mx);
   __syncthreads();
   // The record; then each run's first slot in the copy, from the top run.
@@ -2968,7 +2965,10 @@ __device__ __forceinline__ void store_out(void *out, int64_t off, float v) {
 
 __device__ __forceinline__ int attend_list_len(const Params &p, int b, int L, bool fused) {
   if (!fused) return p.k_max;
-  return p.idx_stride > 0 ? p.idx_stride : row_plan(p, b, L).total;
+  // (the plan first: its parameters then load together with idx_stride, not
+  // a cold round trip after it)
+  const int total = row_plan(p, b, L).total;
+  return p.idx_stride > 0 ? p.idx_stride : total;
 }
 
 // Row index of position j of sequence b in a cache, 32 bits: j itself in
@@ -3888,10 +3888,13 @@ int attend_split(const Params &p, int k_max_positions, bool fused) {
 }
 
 // Per-head rows: threads per workgroup and entries per workgroup.  About
-// kGatherWaves waves in all (16 per CU), each with at least 64 entries; a row
-// of up to 16 waves is one workgroup and needs no merge (a launch of 4-5 us),
-// and so does a row that one workgroup gathers in that time anyway
-// (kGatherWhole bytes).
+// kGatherWaves waves in all, 16 per CU (registers allow no more beside key
+// rows), each with at least 64 entries.  A row of up to 16 waves is one
+// workgroup and needs no merge (a launch of 4-5 us), and so does a row that
+// one workgroup gathers in that time anyway (kGatherWhole bytes).  Other
+// rows are split into 256-thread workgroups, so that all are resident at once
+// (96 rows on 288 workgroups of 1024 threads, one per CU, left most of the
+// chip idle in the second round: 70 against 63 us).
 constexpr int kGatherWaves = 4096;
 constexpr int64_t kGatherWhole = 420 * 1024;
 struct GatherPlan {
@@ -3899,16 +3902,19 @@ struct GatherPlan {
 };
 static GatherPlan gather_plan(int64_t rows, int64_t k, int entry_bytes) {
   k = k > 0 ? k : 1;
-  int64_t waves = (kGatherWaves + rows - 1) / rows;
+  int64_t waves = kGatherWaves / rows;
   const int64_t blocks = (k + 63) / 64;
   waves = waves < blocks ? waves : blocks;
-  if (waves > 16 && k * entry_bytes <= kGatherWhole) waves = 16;
-  GatherPlan pl;
-  pl.nt = waves <= 4 ? 256 : (waves <= 8 ? 512 : 1024);
-  pl.nsplit = (int)((waves + 15) / 16);
-  const int64_t split = ((k + pl.nsplit - 1) / pl.nsplit + 63) / 64 * 64;
-  pl.split = (int)split;
-  pl.nsplit = (int)((k + split - 1) / split);
+  waves = waves > 1 ? waves : 1;
+  GatherPlan pl{256, (int)((k + 63) / 64 * 64), 1};
+  if (waves > 16 && k * entry_bytes > kGatherWhole) {
+    pl.nsplit = (int)(waves / kWaves);
+    pl.split = (int)(((k + pl.nsplit - 1) / pl.nsplit + 63) / 64 * 64);
+    pl.nsplit = (int)((k + pl.split - 1) / pl.split);
+  } else {
+    // (two workgroups of 512 threads fit a CU, one of 1024)
+    pl.nt = waves > 8 && rows <= 256 ? 1024 : (waves > 4 ? 512 : 256);
+  }
   return pl;
 }
 
