@@ -4068,9 +4068,17 @@ hipError_t launch_score_dense(const Params &p, float *scores, hipStream_t st) {
     return p.K.paged ? score_keys<true>(p, scores, true, none, st)
                      : score_keys<false>(p, scores, true, none, st);
   }
-  const int parts = (int)cdiv(p.ncap, kDenseChunk);
-  const dim3 grid(parts, p.B * p.Hkv);
-  const bool pipe = dense_pipelined(p, parts);
+  // Workgroups of 8192 keys, or as many as make about 2048 in all, each wave
+  // with a tile of its own: float32 keys and labels are read a tile at a time
+  // (4096 float32 keys of one head in one workgroup: 290 us; 2 x 8K x 2 heads
+  // 1.17 ms).
+  const int64_t groups = (int64_t)p.B * p.Hkv, tiles = cdiv(p.ncap, kTile);
+  int64_t want = (2048 + groups - 1) / groups;
+  want = want < (int64_t)cdiv(tiles, kWaves) ? want : (int64_t)cdiv(tiles, kWaves);
+  int64_t parts = cdiv(p.ncap, kDenseChunk);
+  parts = parts > want ? parts : want;
+  const dim3 grid((unsigned)parts, p.B * p.Hkv);
+  const bool pipe = dense_pipelined(p, (int)parts);
   if (p.labels) {
     if (pipe) k_score_dense<true, true, true><<<grid, kBlock, 0, st>>>(p, scores, p.ncap);
     else k_score_dense<true, true, false><<<grid, kBlock, 0, st>>>(p, scores, p.ncap);
