@@ -22,6 +22,7 @@ from __future__ import annotations
 import ctypes as C
 import dataclasses
 import os
+import struct
 from typing import Optional
 
 import torch
@@ -67,46 +68,34 @@ class SdProfile(C.Structure):
 
 
 _P = C.POINTER
+_D = C.c_void_p  # a descriptor: byref of its structure, or its packed bytes (see _desc)
 lib = C.CDLL(LIB_PATH)
 lib.sparse_decode_score.restype = C.c_int
-lib.sparse_decode_score.argtypes = [_P(SdTensor), _P(SdKv), C.c_void_p, _P(SdSparsity),
-                                    _P(SdTensor), C.c_void_p]
+lib.sparse_decode_score.argtypes = [_D, _D, C.c_void_p, _D, _D, C.c_void_p]
 lib.sparse_decode_topk.restype = C.c_int
-lib.sparse_decode_topk.argtypes = [_P(SdTensor), C.c_void_p, _P(SdSparsity), _P(SdTensor),
-                                   _P(SdTensor), C.c_void_p]
+lib.sparse_decode_topk.argtypes = [_D, C.c_void_p, _D, _D, _D, C.c_void_p]
 lib.sparse_decode_attend.restype = C.c_int
-lib.sparse_decode_attend.argtypes = [_P(SdTensor), _P(SdKv), _P(SdKv), C.c_void_p, _P(SdTensor),
-                                     _P(SdSparsity), _P(SdTensor), C.c_void_p]
+lib.sparse_decode_attend.argtypes = [_D, _D, _D, C.c_void_p, _D, _D, _D, C.c_void_p]
 lib.sparse_decode_attend_weighted.restype = C.c_int
-lib.sparse_decode_attend_weighted.argtypes = [_P(SdTensor), _P(SdKv), _P(SdKv), C.c_void_p,
-                                              _P(SdTensor), _P(SdTensor), _P(SdSparsity),
-                                              _P(SdTensor), C.c_void_p]
+lib.sparse_decode_attend_weighted.argtypes = [_D, _D, _D, C.c_void_p, _D, _D, _D, _D, C.c_void_p]
 lib.sparse_decode_dense_attention.restype = C.c_int
-lib.sparse_decode_dense_attention.argtypes = [_P(SdTensor), _P(SdKv), _P(SdKv), C.c_void_p,
-                                              C.c_float, _P(SdTensor), C.c_void_p]
+lib.sparse_decode_dense_attention.argtypes = [_D, _D, _D, C.c_void_p, C.c_float, _D, C.c_void_p]
 lib.sparse_decode_dense_workspace_size.restype = C.c_int
-lib.sparse_decode_dense_workspace_size.argtypes = [_P(SdTensor), _P(SdKv), _P(C.c_size_t)]
+lib.sparse_decode_dense_workspace_size.argtypes = [_D, _D, _P(C.c_size_t)]
 lib.sparse_decode_label_attention.restype = C.c_int
-lib.sparse_decode_label_attention.argtypes = [_P(SdTensor), _P(SdKv), _P(SdKv), _P(SdLabels),
-                                              C.c_void_p, _P(SdSparsity), _P(SdTensor),
-                                              _P(SdTensor), C.c_void_p]
+lib.sparse_decode_label_attention.argtypes = [_D, _D, _D, _D, C.c_void_p, _D, _D, _D, C.c_void_p]
 lib.sparse_decode_label_score.restype = C.c_int
-lib.sparse_decode_label_score.argtypes = [_P(SdTensor), _P(SdKv), _P(SdLabels), C.c_void_p,
-                                          _P(SdSparsity), _P(SdTensor), C.c_void_p]
+lib.sparse_decode_label_score.argtypes = [_D, _D, _D, C.c_void_p, _D, _D, C.c_void_p]
 lib.sparse_decode_attention.restype = C.c_int
-lib.sparse_decode_attention.argtypes = [_P(SdTensor), _P(SdKv), _P(SdKv), C.c_void_p,
-                                        _P(SdSparsity), _P(SdTensor), _P(SdTensor), C.c_void_p]
+lib.sparse_decode_attention.argtypes = [_D, _D, _D, C.c_void_p, _D, _D, _D, C.c_void_p]
 lib.sparse_decode_attention_noalloc.restype = C.c_int
-lib.sparse_decode_attention_noalloc.argtypes = [_P(SdTensor), _P(SdKv), _P(SdKv), C.c_void_p,
-                                                _P(SdSparsity), _P(SdTensor), _P(SdTensor),
-                                                C.c_void_p]
+lib.sparse_decode_attention_noalloc.argtypes = [_D, _D, _D, C.c_void_p, _D, _D, _D, C.c_void_p]
 lib.sparse_decode_workspace_size.restype = C.c_int
-lib.sparse_decode_workspace_size.argtypes = [_P(SdTensor), _P(SdKv), _P(SdSparsity), _P(SdTensor),
-                                             _P(C.c_size_t)]
+lib.sparse_decode_workspace_size.argtypes = [_D, _D, _D, _D, _P(C.c_size_t)]
 lib.sparse_decode_set_workspace.restype = C.c_int
 lib.sparse_decode_set_workspace.argtypes = [C.c_void_p, C.c_size_t]
 lib.sparse_decode_budget.restype = C.c_int64
-lib.sparse_decode_budget.argtypes = [C.c_int64, _P(SdSparsity)]
+lib.sparse_decode_budget.argtypes = [C.c_int64, _D]
 lib.sparse_decode_set_profiling.restype = C.c_int
 lib.sparse_decode_set_profiling.argtypes = [C.c_int32]
 lib.sparse_decode_last_profile.restype = C.c_int
@@ -116,9 +105,8 @@ lib.sparse_decode_profile_mean.argtypes = [_P(SdProfile), _P(C.c_int32)]
 lib.sparse_decode_set_debug.restype = C.c_int
 lib.sparse_decode_set_debug.argtypes = [C.c_int32]
 lib.sparse_decode_sampled_attention.restype = C.c_int
-lib.sparse_decode_sampled_attention.argtypes = [_P(SdTensor), _P(SdKv), _P(SdKv), C.c_void_p,
-                                                _P(SdSparsity), _P(SdTensor), _P(SdTensor),
-                                                _P(SdTensor), _P(SdTensor), C.c_void_p]
+lib.sparse_decode_sampled_attention.argtypes = [_D, _D, _D, C.c_void_p, _D, _D, _D, _D, _D,
+                                                C.c_void_p]
 lib.sparse_decode_read_probe.restype = C.c_int
 lib.sparse_decode_read_probe.argtypes = [C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p]
 lib.sparse_decode_status_string.restype = C.c_char_p
@@ -241,15 +229,79 @@ def _tensor(t: torch.Tensor, name: str) -> SdTensor:
     return st
 
 
+# The calls below pass descriptors as packed bytes in the structures' native
+# layout: filling a ctypes structure field by field took 2-4 us per tensor,
+# 17 of the 20 us that a small call spent on the host.
+_PACK_TENSOR = struct.Struct("@Pii4q")
+_PACK_KV = struct.Struct("@Pii4qiIPi4x")
+_PACK_SPARSITY = struct.Struct("@dIIfPII")
+_PACK_LABELS = struct.Struct("@Pii4qP")
+for _s, _t in ((_PACK_TENSOR, SdTensor), (_PACK_KV, SdKv), (_PACK_SPARSITY, SdSparsity),
+               (_PACK_LABELS, SdLabels)):
+    if _s.size != C.sizeof(_t):
+        raise ImportError(f"descriptor layout of {_t.__name__} does not match")
+_U32 = 0xFFFFFFFF  # int32 fields wrap, as a ctypes structure's do
+_PAD = ((0, 0, 0, 0), (0, 0, 0), (0, 0), (0,), ())
+
+
+def _fields(t: torch.Tensor, name: str) -> tuple:
+    """The sd_tensor fields of t, in order (the checks of _tensor)."""
+    if not isinstance(t, torch.Tensor) or not t.is_cuda or not t.is_contiguous():
+        _need_device(t, name)  # raises
+    dtype = _DTYPES.get(t.dtype)
+    if dtype is None:
+        raise ValueError(f"{name}: unsupported dtype {t.dtype}")
+    shape = t.shape
+    n = len(shape)
+    if n > 4:
+        raise ValueError(f"{name}: at most 4 dimensions")
+    return (0 if 0 in shape else t.data_ptr(), dtype, n, *shape, *_PAD[n])
+
+
+def _desc(t: torch.Tensor, name: str) -> bytes:
+    return _PACK_TENSOR.pack(*_fields(t, name))
+
+
+def _kv_desc(cache: KVCache, *which: str):
+    """KVCache.c(which) as packed bytes (a tuple of them for several)."""
+    if cache.layout == "paged":
+        bt = cache.block_table
+        _need_device(bt, "block_table", torch.int32)
+        tail = (SD_KV_PAGED_NHD, cache.page_size & _U32, bt.data_ptr(), bt.shape[1])
+    elif cache.layout == "bhnd":
+        tail = (SD_KV_BHND, 0, 0, 0)
+    else:
+        raise ValueError(f"unknown layout {cache.layout!r}")
+    got = tuple(_PACK_KV.pack(*_fields(cache.k if w == "k" else cache.v, w), *tail) for w in which)
+    return got if len(got) > 1 else got[0]
+
+
+def _sparsity_desc(sp: Sparsity) -> bytes:
+    """Sparsity.c() as packed bytes."""
+    ko = sp.k_override
+    if ko is not None:
+        _need_device(ko, "k_override", torch.int32)
+    return _PACK_SPARSITY.pack(float(sp.ratio), int(sp.rounding) & _U32, int(bool(sp.group_shared)),
+                               C.c_float(sp.softmax_scale).value,
+                               ko.data_ptr() if ko is not None else 0,
+                               int(sp.n_sink) & _U32, int(sp.n_local) & _U32)
+
+
+def _labels_desc(labels: Labels) -> bytes:
+    """Labels.c() as packed bytes."""
+    _need_device(labels.channels, "channels", torch.int32)
+    return _PACK_LABELS.pack(*_fields(labels.t, "labels"), labels.channels.data_ptr())
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def budget(L: int, sparsity: Sparsity) -> int:
     """k for a sequence of L positions under the ratio rule."""
-    return int(lib.sparse_decode_budget(int(L), C.byref(sparsity.c())))
+    return int(lib.sparse_decode_budget(int(L), _sparsity_desc(sparsity)))
 
 
 def rows_of(q: torch.Tensor, cache: KVCache, sparsity: Sparsity) -> int:
@@ -266,9 +318,10 @@ def sparse_decode_score(q, cache: KVCache, seq_lens, sparsity: Sparsity, scores=
     if scores is None:
         scores = torch.empty((q.shape[0], rows_of(q, cache, sparsity), cache.capacity),
                              dtype=torch.float32, device=q.device)
-    sp, kq, kk, ks = sparsity.c(), _tensor(q, "q"), cache.c("k"), _tensor(scores, "scores")
-    _check(lib.sparse_decode_score(C.byref(kq), C.byref(kk), seq_lens.data_ptr(), C.byref(sp),
-                                   C.byref(ks), _stream(stream)), "sparse_decode_score")
+    sp, kq, kk = _sparsity_desc(sparsity), _desc(q, "q"), _kv_desc(cache, "k")
+    ks = _desc(scores, "scores")
+    _check(lib.sparse_decode_score(kq, kk, seq_lens.data_ptr(), sp, ks, _stream(stream)),
+           "sparse_decode_score")
     return scores
 
 
@@ -283,10 +336,9 @@ def sparse_decode_topk(scores, seq_lens, sparsity: Sparsity, k_max: Optional[int
                           device=scores.device)
     if with_vals and vals is None:
         vals = torch.empty(idx.shape, dtype=torch.float32, device=scores.device)
-    sp, cs, ci = sparsity.c(), _tensor(scores, "scores"), _tensor(idx, "idx")
-    cv = _tensor(vals, "vals") if vals is not None else None
-    _check(lib.sparse_decode_topk(C.byref(cs), seq_lens.data_ptr(), C.byref(sp), C.byref(ci),
-                                  C.byref(cv) if cv is not None else None, _stream(stream)),
+    sp, cs, ci = _sparsity_desc(sparsity), _desc(scores, "scores"), _desc(idx, "idx")
+    cv = _desc(vals, "vals") if vals is not None else None
+    _check(lib.sparse_decode_topk(cs, seq_lens.data_ptr(), sp, ci, cv, _stream(stream)),
            "sparse_decode_topk")
     return (idx, vals) if vals is not None else idx
 
@@ -297,11 +349,11 @@ def sparse_decode_attend(q, cache: KVCache, seq_lens, idx, sparsity: Sparsity, o
     _need_device(seq_lens, "seq_lens", torch.int32)
     if out is None:
         out = torch.empty_like(q)
-    sp = sparsity.c()
-    cq, kk, kv = _tensor(q, "q"), cache.c("k"), cache.c("v")
-    ci, co = _tensor(idx, "idx"), _tensor(out, "out")
-    _check(lib.sparse_decode_attend(C.byref(cq), C.byref(kk), C.byref(kv), seq_lens.data_ptr(),
-                                    C.byref(ci), C.byref(sp), C.byref(co), _stream(stream)),
+    sp = _sparsity_desc(sparsity)
+    cq, (kk, kv) = _desc(q, "q"), _kv_desc(cache, "k", "v")
+    ci, co = _desc(idx, "idx"), _desc(out, "out")
+    _check(lib.sparse_decode_attend(cq, kk, kv, seq_lens.data_ptr(), ci, sp, co,
+                                    _stream(stream)),
            "sparse_decode_attend")
     return out
 
@@ -314,12 +366,11 @@ def sparse_decode_attend_weighted(q, cache: KVCache, seq_lens, idx, weights, spa
     _need_device(weights, "weights", torch.float32)
     if out is None:
         out = torch.empty_like(q)
-    sp = sparsity.c()
-    cq, kk, kv = _tensor(q, "q"), cache.c("k"), cache.c("v")
-    ci, cw, co = _tensor(idx, "idx"), _tensor(weights, "weights"), _tensor(out, "out")
-    _check(lib.sparse_decode_attend_weighted(C.byref(cq), C.byref(kk), C.byref(kv),
-                                             seq_lens.data_ptr(), C.byref(ci), C.byref(cw),
-                                             C.byref(sp), C.byref(co), _stream(stream)),
+    sp = _sparsity_desc(sparsity)
+    cq, (kk, kv) = _desc(q, "q"), _kv_desc(cache, "k", "v")
+    ci, cw, co = _desc(idx, "idx"), _desc(weights, "weights"), _desc(out, "out")
+    _check(lib.sparse_decode_attend_weighted(cq, kk, kv, seq_lens.data_ptr(), ci, cw, sp, co,
+                                             _stream(stream)),
            "sparse_decode_attend_weighted")
     return out
 
@@ -330,18 +381,18 @@ def sparse_decode_dense_attention(q, cache: KVCache, seq_lens, softmax_scale: fl
     _need_device(seq_lens, "seq_lens", torch.int32)
     if out is None:
         out = torch.empty_like(q)
-    cq, kk, kv, co = _tensor(q, "q"), cache.c("k"), cache.c("v"), _tensor(out, "out")
-    _check(lib.sparse_decode_dense_attention(C.byref(cq), C.byref(kk), C.byref(kv),
+    cq, (kk, kv), co = _desc(q, "q"), _kv_desc(cache, "k", "v"), _desc(out, "out")
+    _check(lib.sparse_decode_dense_attention(cq, kk, kv,
                                              seq_lens.data_ptr(), float(softmax_scale),
-                                             C.byref(co), _stream(stream)),
+                                             co, _stream(stream)),
            "sparse_decode_dense_attention")
     return out
 
 
 def dense_workspace_size(q, cache: KVCache) -> int:
     n = C.c_size_t(0)
-    cq, kk = _tensor(q, "q"), cache.c("k")
-    _check(lib.sparse_decode_dense_workspace_size(C.byref(cq), C.byref(kk), C.byref(n)),
+    cq, kk = _desc(q, "q"), _kv_desc(cache, "k")
+    _check(lib.sparse_decode_dense_workspace_size(cq, kk, C.byref(n)),
            "sparse_decode_dense_workspace_size")
     return int(n.value)
 
@@ -357,11 +408,11 @@ def sparse_decode_attention(q, cache: KVCache, seq_lens, sparsity: Sparsity, out
             k_max = k_max_of(cache, sparsity)
         idx = torch.empty((q.shape[0], rows_of(q, cache, sparsity), k_max), dtype=torch.int32,
                           device=q.device)
-    sp = sparsity.c()
-    cq, kk, kv = _tensor(q, "q"), cache.c("k"), cache.c("v")
-    co, ci = _tensor(out, "out"), _tensor(idx, "idx")
-    _check(lib.sparse_decode_attention(C.byref(cq), C.byref(kk), C.byref(kv), seq_lens.data_ptr(),
-                                       C.byref(sp), C.byref(co), C.byref(ci), _stream(stream)),
+    sp = _sparsity_desc(sparsity)
+    cq, (kk, kv) = _desc(q, "q"), _kv_desc(cache, "k", "v")
+    co, ci = _desc(out, "out"), _desc(idx, "idx")
+    _check(lib.sparse_decode_attention(cq, kk, kv, seq_lens.data_ptr(), sp, co, ci,
+                                       _stream(stream)),
            "sparse_decode_attention")
     return out, idx
 
@@ -374,12 +425,11 @@ def sparse_decode_attention_noalloc(q, cache: KVCache, seq_lens, sparsity: Spars
     """The fused method with the library's static scratch instead of its
     workspace (no device allocation); out and idx are the caller's."""
     _need_device(seq_lens, "seq_lens", torch.int32)
-    sp = sparsity.c()
-    cq, kk, kv = _tensor(q, "q"), cache.c("k"), cache.c("v")
-    co, ci = _tensor(out, "out"), _tensor(idx, "idx")
-    _check(lib.sparse_decode_attention_noalloc(C.byref(cq), C.byref(kk), C.byref(kv),
-                                               seq_lens.data_ptr(), C.byref(sp), C.byref(co),
-                                               C.byref(ci), _stream(stream)),
+    sp = _sparsity_desc(sparsity)
+    cq, (kk, kv) = _desc(q, "q"), _kv_desc(cache, "k", "v")
+    co, ci = _desc(out, "out"), _desc(idx, "idx")
+    _check(lib.sparse_decode_attention_noalloc(cq, kk, kv, seq_lens.data_ptr(), sp, co, ci,
+                                               _stream(stream)),
            "sparse_decode_attention_noalloc")
     return out, idx
 
@@ -396,12 +446,11 @@ def sparse_decode_label_attention(q, cache: KVCache, labels: Labels, seq_lens, s
             k_max = k_max_of(cache, sparsity)
         idx = torch.empty((q.shape[0], rows_of(q, cache, sparsity), k_max), dtype=torch.int32,
                           device=q.device)
-    sp, lab = sparsity.c(), labels.c()
-    cq, kk, kv = _tensor(q, "q"), cache.c("k"), cache.c("v")
-    co, ci = _tensor(out, "out"), _tensor(idx, "idx")
-    _check(lib.sparse_decode_label_attention(C.byref(cq), C.byref(kk), C.byref(kv), C.byref(lab),
-                                             seq_lens.data_ptr(), C.byref(sp), C.byref(co),
-                                             C.byref(ci), _stream(stream)),
+    sp, lab = _sparsity_desc(sparsity), _labels_desc(labels)
+    cq, (kk, kv) = _desc(q, "q"), _kv_desc(cache, "k", "v")
+    co, ci = _desc(out, "out"), _desc(idx, "idx")
+    _check(lib.sparse_decode_label_attention(cq, kk, kv, lab, seq_lens.data_ptr(), sp, co, ci,
+                                             _stream(stream)),
            "sparse_decode_label_attention")
     return out, idx
 
@@ -413,18 +462,18 @@ def sparse_decode_label_score(q, cache: KVCache, labels: Labels, seq_lens, spars
     if scores is None:
         scores = torch.empty((q.shape[0], rows_of(q, cache, sparsity), cache.capacity),
                              dtype=torch.float32, device=q.device)
-    sp, lab = sparsity.c(), labels.c()
-    cq, kk, ks = _tensor(q, "q"), cache.c("k"), _tensor(scores, "scores")
-    _check(lib.sparse_decode_label_score(C.byref(cq), C.byref(kk), C.byref(lab),
-                                         seq_lens.data_ptr(), C.byref(sp), C.byref(ks),
+    sp, lab = _sparsity_desc(sparsity), _labels_desc(labels)
+    cq, kk, ks = _desc(q, "q"), _kv_desc(cache, "k"), _desc(scores, "scores")
+    _check(lib.sparse_decode_label_score(cq, kk, lab, seq_lens.data_ptr(), sp, ks,
                                          _stream(stream)), "sparse_decode_label_score")
     return scores
 
 
 def workspace_size(q, cache: KVCache, sparsity: Sparsity, idx) -> int:
     n = C.c_size_t(0)
-    sp, cq, kk, ci = sparsity.c(), _tensor(q, "q"), cache.c("k"), _tensor(idx, "idx")
-    _check(lib.sparse_decode_workspace_size(C.byref(cq), C.byref(kk), C.byref(sp), C.byref(ci),
+    sp, cq, kk = _sparsity_desc(sparsity), _desc(q, "q"), _kv_desc(cache, "k")
+    ci = _desc(idx, "idx")
+    _check(lib.sparse_decode_workspace_size(cq, kk, sp, ci,
                                             C.byref(n)), "sparse_decode_workspace_size")
     return int(n.value)
 
@@ -483,13 +532,11 @@ def sparse_decode_sampled_attention(q, cache: KVCache, seq_lens, sparsity: Spars
         weights = torch.empty(idx.shape, dtype=torch.float32, device=q.device)
     if out is None:
         out = torch.empty_like(q)
-    sp = sparsity.c()
-    cq, kk, kv = _tensor(q, "q"), cache.c("k"), cache.c("v")
-    cd, co, ci, cw = _tensor(draws, "draws"), _tensor(out, "out"), _tensor(idx, "idx"), \
-        _tensor(weights, "weights")
-    _check(lib.sparse_decode_sampled_attention(C.byref(cq), C.byref(kk), C.byref(kv),
-                                               seq_lens.data_ptr(), C.byref(sp), C.byref(cd),
-                                               C.byref(co), C.byref(ci), C.byref(cw),
+    sp = _sparsity_desc(sparsity)
+    cq, (kk, kv) = _desc(q, "q"), _kv_desc(cache, "k", "v")
+    cd, co, ci, cw = _desc(draws, "draws"), _desc(out, "out"), _desc(idx, "idx"), \
+        _desc(weights, "weights")
+    _check(lib.sparse_decode_sampled_attention(cq, kk, kv, seq_lens.data_ptr(), sp, cd, co, ci, cw,
                                                _stream(stream)),
            "sparse_decode_sampled_attention")
     return out, idx, weights
