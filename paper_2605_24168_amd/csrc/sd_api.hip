@@ -354,8 +354,23 @@ bool full_scores_pay(const Shape &s, bool labels) {
   return 1.2 * scores + 8.0 * len + 9.0 * key_gb - 5.0 * (s.B * s.Hkv / 128.0) < 13.0;
 }
 
+// Fewest units of the persistent stream (a chunk of one KV head, or of four
+// in the four-heads form) that a call is given where halving its waves can:
+// a unit of 2 MB keeps its compute unit for 70-80 us, so with at most half of
+// the 256 compute units busy halving costs nothing and halves the stream (32
+// heads on 8 KV heads, paged, 2 x 64K keys, 128 units: 102 -> 91 us; 1 x 128K:
+// 104 -> 94 us).  Not beyond: units of half the size are 3-5 us longer for
+// the same keys (drain, packing, more chunks per row for the selection), and
+// calls that fill whole rounds of the chip lose that (8 x 64K, 512 units: 227
+// -> 238 us; 4 x 64K, 256 units: 133 -> 139 us), though a ragged batch, whose
+// lengths the host does not know, gains (8 x 4K-64K: 194 -> 173 us).
+constexpr int64_t kStreamUnitsMin = 256;
+constexpr int kWaveKeysHalved = 512;  // shortest waves that halving makes
+
+// halve: whether waves may be halved for a call of few units (their blocks
+// take more workspace; the results are the same).
 Layout layout_for(const Shape &s, int64_t k_max, bool fused, const sd_sparsity *sp,
-                  bool labels = false, bool allow_union = true) {
+                  bool labels = false, bool allow_union = true, bool halve = true) {
   Layout L{};
   const int group_shared = sp->group_shared ? 1 : 0;
   const int64_t rows = (int64_t)s.B * s.R;
@@ -366,6 +381,16 @@ Layout layout_for(const Shape &s, int64_t k_max, bool fused, const sd_sparsity *
   // selection's per-chunk tables.
   const int64_t qchunks = (s.ncap + L.wave_keys - 1) / L.wave_keys;
   const bool quad = s.paged && s.Hkv % sd::kWaves == 0 && qchunks <= 8192;
+  if (halve && fused && !labels) {
+    const int64_t heads = (int64_t)s.B * (quad ? s.Hkv / sd::kWaves : s.Hkv);
+    const int waves = quad ? 1 : sd::kWaves;
+    auto chunks = [&](int wk) { return (s.ncap + (int64_t)waves * wk - 1) / (waves * wk); };
+    // (nor beyond the chunks that the selection in pieces can take)
+    while (L.wave_keys > kWaveKeysHalved && 2 * heads * chunks(L.wave_keys) <= kStreamUnitsMin &&
+           psel_parts_for(s, (int)chunks(L.wave_keys / 2)) >=
+               psel_parts_for(s, (int)chunks(L.wave_keys)))
+      L.wave_keys /= 2;
+  }
   L.chunk_keys = quad ? L.wave_keys : sd::kWaves * L.wave_keys;
   L.blk_cap = quad ? sd::kCandBuf : sd::kChunkCap;
   L.nchunk = (int)((s.ncap + L.chunk_keys - 1) / L.chunk_keys);
@@ -783,14 +808,16 @@ sd_status attention_impl(const sd_tensor *q, const sd_kv *K, const sd_kv *V,
   std::lock_guard<std::mutex> lk(g_mu);
   // (the sampled call's unfused weighted attention needs partials for the
   // whole list, and no union attention)
-  const Layout L = layout_for(s, smp ? k_list : k_max, true, sp, labels != nullptr, !smp);
+  Layout L = layout_for(s, smp ? k_list : k_max, true, sp, labels != nullptr, !smp);
+  DevState *ds = nullptr;
+  st = device_state(ds);
+  if (st) return st;
+  if (L.total > (no_alloc ? kScratchBytes : ds->user_ws ? ds->ws_bytes : SIZE_MAX))
+    L = layout_for(s, smp ? k_list : k_max, true, sp, labels != nullptr, !smp, false);
   // One scoring workgroup per (chunk, sequence, KV head) on a 1-D grid.
   if ((int64_t)L.nchunk * s.B * s.Hkv > INT32_MAX) return SD_ERR_UNSUPPORTED;
-  DevState *ds = nullptr;
   char *base = nullptr;
   if (no_alloc) {  // the static scratch: nothing allocated, sizes beyond it refused
-    st = device_state(ds);
-    if (st) return st;
     if (L.total > kScratchBytes) return SD_ERR_WORKSPACE;
     base = (char *)ds->scratch;
   } else {

@@ -82,3 +82,47 @@ def test_short_context_rule(sd, kind, layout, Hq, Hkv, lens, ncap):
         np.testing.assert_array_equal(x, y)
     if kind != "noalloc":  # (its calls are not profiled)
         assert full > 0 and cand < full, (full, cand)
+
+
+@pytest.mark.parametrize("layout,lens,Hq,Hkv", [
+    ("paged", [32768], 32, 8),          # 32 units of 2048-key waves, halved twice
+    ("paged", [65536, 1025], 8, 4),     # 64 units: at 512 keys a whole round
+    ("paged", [1024, 1023, 513], 12, 6),  # one head per workgroup, under a chunk
+    ("bhnd", [131071], 8, 2),           # 32 units, the last chunk one key short
+])
+def test_halved_waves(sd, layout, lens, Hq, Hkv):
+    """Calls of few stream units run shorter waves where their workspace has
+    room; both give the lists of the full-score path."""
+    inp = synth.make_inputs(2, seed=5, seq_lens=lens, ncap=max(lens), Hq=Hq, Hkv=Hkv,
+                            layout=layout, ratio=40.0)
+    q, cache, sl = sd.cache_from_inputs(inp)
+    sp = sd.sparsity_from_inputs(inp)
+    kmax = O.k_max_for(inp)
+    idx = torch.empty((inp.B, Hq, kmax), dtype=torch.int32, device="cuda")
+    buf = torch.empty(sd.workspace_size(q, cache, sp, idx), dtype=torch.uint8, device="cuda")
+
+    def call(flags, room):
+        sd.set_debug(flags)
+        sd.set_workspace(buf[:room])
+        try:
+            out = [P.to_host(t) for t in sd.sparse_decode_attention(q, cache, sl, sp, k_max=kmax)]
+            torch.cuda.synchronize()
+            return out
+        finally:
+            sd.set_workspace(None)
+            sd.set_debug(0)
+
+    # The smallest workspace that is taken (too small ones launch nothing):
+    # the one of whole-length waves.
+    lo, hi = 0, buf.numel() // 256
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        try:
+            call(CANDIDATES, 256 * mid)
+            hi = mid
+        except sd.SparseDecodeError:
+            lo = mid
+    got = [call(0, buf.numel()), call(CANDIDATES, buf.numel()), call(CANDIDATES, 256 * hi)]
+    for other in got[1:]:
+        for x, y in zip(got[0], other):
+            np.testing.assert_array_equal(x, y)
