@@ -1835,8 +1835,8 @@ __device__ __forceinline__ void select_regs(const ChunkCands &src, int n, int k,
 constexpr int kRankMax = 64;   // keys of a bucket worth an exact rank count
 constexpr int kRowSlots = 16;  // scores per thread of a row kept whole in registers
 
-// A score's key, never 0: lanes without an item hold key 0, below every
-// bucket and threshold of the functions below.
+// A score's key, never 0: lanes without an item hold key 0, which the
+// functions below keep out of every bucket (from 1 up) and threshold.
 __device__ __forceinline__ uint32_t row_key(float f) {
   const uint32_t x = f2key(f);
   return x > 1u ? x : 1u;
@@ -1856,8 +1856,8 @@ __device__ __forceinline__ void wave_hist(uint32_t *hist, int bk, bool in) {
 }
 
 // The block's items are the nonzero keys of slots u < U; hist holds their
-// counts in the buckets kb, published.  Returns the bucket [blo, bhi] of the
-// krem-th largest key, narrowed by further histograms until it holds at most
+// counts in the buckets kb, published.  Returns the bucket [blo, bhi] (blo at
+// least 1) of the krem-th largest key, narrowed by further histograms until it holds at most
 // mmax keys or one key value, and the keys it holds; krem becomes the rank
 // inside it.  Keys past the last bucket of kb are counted in it.  hist2:
 // zero and published too.  Ends with a barrier.
@@ -1871,8 +1871,10 @@ __device__ __forceinline__ int narrow_bucket(const uint32_t (&key)[UMAX], int U,
     const uint32_t b = sh->digit;
     const int m = (int)hist[b];
     krem -= sh->above;
-    blo = kb.lo + (b << kb.shift);
-    if (b < (uint32_t)kBuckets - 1u) bhi = blo + ((1u << kb.shift) - 1u);  // (else the range's end)
+    const uint32_t first = kb.lo + (b << kb.shift), last = first + ((1u << kb.shift) - 1u);
+    blo = first > 1u ? first : 1u;  // (not the empty lanes' key 0: hist has not counted them)
+    // (the last bucket ends where the range does, which may be inside it)
+    if (b < (uint32_t)kBuckets - 1u && last >= first && last < bhi) bhi = last;
     if (m <= mmax || blo == bhi) {
       __syncthreads();  // sh is reused
       return m;

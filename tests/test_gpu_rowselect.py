@@ -81,6 +81,22 @@ def test_topk_rows(sd, kind, rows, n, ratio):
     check(sd, rows_of_kind(kind, rows, n), n, ratio)
 
 
+@pytest.mark.parametrize("rows,n,nans", [(2, 100, 100), (2, 1040, 64), (3, 1040, 1040), (1, 16384, 200),
+                                         (513, 4095, 300)])
+def test_topk_rows_of_the_lowest_nans(sd, rows, n, nans):
+    # Every position kept, the k-th key being that of the lowest NaN, in the
+    # bucket where lanes without a score would be counted too: the lists hold
+    # each position once.
+    s = np.random.default_rng(n).standard_normal((1, rows, n), dtype=np.float32)
+    s.view(np.uint32)[:, :, :nans] = 0xFFFFFFFF
+    idx, vals = sd.sparse_decode_topk(torch.from_numpy(s).cuda(),
+                                      torch.tensor([n], dtype=torch.int32, device="cuda"),
+                                      sd.Sparsity(ratio=1.0), with_vals=True)
+    torch.cuda.synchronize()
+    assert (idx.cpu().numpy() == np.arange(n)).all()
+    np.testing.assert_array_equal(vals.cpu().numpy(), s)
+
+
 @pytest.mark.parametrize("L", [0, 1, 63, 16500, 50000])
 def test_topk_forced_and_short_sequences(sd, L):
     if L == 0:
