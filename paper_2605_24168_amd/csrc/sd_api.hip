@@ -257,7 +257,7 @@ struct Layout {
 // logits are recomputed (label selection or forced positions), bf16 GQA.
 bool union_eligible(const Shape &s, const sd_sparsity *sp, bool labels) {
   return !sp->group_shared && s.G >= 2 && s.bf16 && s.ncap > 0 &&
-         (labels || sp->n_sink + sp->n_local > 0);
+         (labels || sd::has_forced(sp->n_sink, sp->n_local));
 }
 
 // Whether it is faster than per-head lists: each head's k_max kept rows

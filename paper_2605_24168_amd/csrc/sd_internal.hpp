@@ -251,6 +251,12 @@ __device__ __forceinline__ RowPlan row_plan(const Params &p, int b, int L) {
   return row_plan(L, p.n_sink, p.n_local, k, p.k_max);
 }
 
+// Whether rows keep forced positions.  (Each field on its own: their sum may
+// pass 32 bits, both meaning "everything" when they are large.)
+__host__ __device__ inline bool has_forced(int n_sink, int n_local) {
+  return n_sink > 0 || n_local > 0;
+}
+
 // Element offset of channel 0 of (sequence b, KV head g, position j).
 __device__ __forceinline__ int64_t kv_offset(const KvView &kv, int b, int g, int64_t j) {
   if (!kv.paged) return (((int64_t)b * kv.hkv + g) * kv.ncap + j) * kHeadDim;

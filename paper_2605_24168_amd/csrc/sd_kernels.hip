@@ -2576,7 +2576,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
   const RowPlan rp = row_plan(p, b, L);
   // (the attention wants finished weights where the list is the top-k alone,
   // scores where other entries share its softmax)
-  const bool weights = MODE != 1 && p.n_sink + p.n_local == 0 && p.idx_stride == 0 && vals != nullptr;
+  const bool weights = MODE != 1 && !has_forced(p.n_sink, p.n_local) && p.idx_stride == 0 && vals != nullptr;
   const int k = rp.kh;
   const int64_t ist = p.idx_stride > 0 ? p.idx_stride : p.k_max;  // list row stride
   int32_t *lrow = idx + (int64_t)row * ist;
@@ -3970,7 +3970,7 @@ template <bool BF16>
 static hipError_t launch_gather(const Params &p, const Work &w, const int32_t *idx, void *out,
                                 bool fused, hipStream_t st) {
   const bool keys = !fused || p.labels;
-  const bool scores = !keys && (p.n_sink + p.n_local > 0 || p.idx_stride > 0);
+  const bool scores = !keys && (has_forced(p.n_sink, p.n_local) || p.idx_stride > 0);
   const int64_t list = fused && p.idx_stride > 0 ? p.idx_stride : p.k_max;
   const int row_bytes = kHeadDim * (BF16 ? 2 : 4);
   const GatherPlan pl = gather_plan((int64_t)p.B * p.R, list, keys ? 2 * row_bytes : row_bytes);

@@ -167,3 +167,19 @@ def test_forced_windows_union_attention(sd, Hq, Hkv, flags):
     finally:
         sd.set_debug(0)
     check(inp, out, idx, f"union {Hq}/{Hkv} flags {flags}")
+
+
+@pytest.mark.parametrize("dtype,n", [("bf16", 3000), ("bf16", 70001), ("f32", 2000)])
+@pytest.mark.parametrize("n_sink,n_local", [(4, 2**31 - 1), (2**31 - 1, 2**31 - 1)])
+def test_windows_that_keep_everything(sd, dtype, n, n_sink, n_local):
+    # Windows past any sequence, their sum past 32 bits: every position kept.
+    inp = synth.make_inputs(2, seed=4, seq_lens=[n, n // 2 + 1, 1], ncap=n + 9, Hq=4, Hkv=2,
+                            dtype=dtype, n_sink=n_sink, n_local=n_local)
+    q, cache, lens = sd.cache_from_inputs(inp)
+    out, idx = sd.sparse_decode_attention(q, cache, lens, sd.sparsity_from_inputs(inp))
+    torch.cuda.synchronize()
+    got = idx.cpu().numpy()
+    want = np.where(np.arange(got.shape[2]) < inp.seq_lens[:, None], np.arange(got.shape[2]), -1)
+    assert (got == want[:, None]).all()
+    ok, worst, _ = P.out_errors(P.to_host(out), O.attend(inp, got)[0], dtype)
+    assert ok, worst
