@@ -3043,16 +3043,19 @@ struct GatherAcc {
   uint32_t qp[4];    // bf16: the same as bf16 pairs
 };
 
-// Sum over the 16 lanes of a DPP row, in every lane of it.
+// Sum over the 16 lanes of a DPP row, the same bits in every lane of it (each
+// step adds a pair of sums that both its lanes hold; rotations would add in
+// another order on every lane, and the lanes of an entry would disagree on its
+// weight).
 __device__ __forceinline__ float row_sum16(float v) {
-  auto ror = [&](auto c) {
+  auto other = [&](auto c) {
     return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(
         0, (int)__float_as_uint(v), decltype(c)::value, 0xf, 0xf, false));
   };
-  v += ror(std::integral_constant<int, 0x121>{});  // row_ror:1, 2, 4, 8
-  v += ror(std::integral_constant<int, 0x122>{});
-  v += ror(std::integral_constant<int, 0x124>{});
-  v += ror(std::integral_constant<int, 0x128>{});
+  v += other(std::integral_constant<int, 0xB1>{});   // quad_perm [1, 0, 3, 2]
+  v += other(std::integral_constant<int, 0x4E>{});   // quad_perm [2, 3, 0, 1]
+  v += other(std::integral_constant<int, 0x141>{});  // row_half_mirror
+  v += other(std::integral_constant<int, 0x140>{});  // row_mirror
   return v;
 }
 

@@ -88,3 +88,23 @@ def test_forced_windows_join_the_scores(sd, dtype, n_sink, n_local, ratio):
     ref = O.attend(inp, idx.cpu().numpy())[0]
     ok, worst, _ = P.out_errors(P.to_host(out), ref, dtype)
     assert ok, worst
+
+
+@pytest.mark.parametrize("k", [2, 40, 500, 4999])
+def test_lanes_of_an_entry_agree(sd, k):
+    # Every channel of a value row holds the same number, so the sums over
+    # the entries are the same in every channel, bit for bit, if the lanes
+    # that share an entry weight it alike.  Logits of 3000 +- 1: an ulp of
+    # one is 2.4e-4 of its weight.
+    g = torch.Generator(device="cuda").manual_seed(k)
+    n = 5000
+    u = torch.nn.functional.normalize(torch.randn((1, 2, 1, 128), generator=g, device="cuda"), dim=-1)
+    q = 60 * u[:, :, 0]
+    kk = 50 * u + torch.randn((1, 2, n, 128), generator=g, device="cuda") / 60
+    v = torch.randn((1, 2, n, 1), generator=g, device="cuda").expand(1, 2, n, 128).contiguous()
+    cache = sd.KVCache(k=kk, v=v)
+    lens = torch.tensor([n], dtype=torch.int32, device="cuda")
+    idx = torch.stack([torch.randperm(n, generator=g, device="cuda")[:k].sort().values
+                       for _ in range(2)]).to(torch.int32)[None]
+    out = sd.sparse_decode_attend(q, cache, lens, idx, sd.Sparsity(ratio=1.0, softmax_scale=1.0))
+    assert torch.equal(out, out[..., :1].expand_as(out))
