@@ -3087,10 +3087,12 @@ __device__ __forceinline__ void gather_entries(const Params &p, int b, int g, in
     float z;
   };
   auto fetch = [&](int n, Raw &r) {
+    // (lanes past the share's end repeat its last entry's row, not a row that
+    // no list keeps, without its weight)
     const int t = t0 + 64 * n + l, tc = t < t1 ? t : t1 - 1;
     r.j = irow[tc];
     r.s = KEYS ? (wrow ? wrow[tc] : 1.f) : srow[tc];
-    if (t >= t1) r.j = -1;
+    if (t >= t1) r.s = SCORES ? -__builtin_inff() : 0.f;
   };
   auto resolve = [&](const Raw &r, Block &bk) {
     const bool in = r.j >= 0 && r.j < L;
@@ -3141,7 +3143,9 @@ __device__ __forceinline__ void gather_entries(const Params &p, int b, int g, in
 #pragma unroll
           for (int e = 0; e < 8; ++e) d = fmaf(st.q[e], kv[e], d);
         }
-        z[u] += p.scale * row_sum16(d);
+        // (a skipped entry stays out whatever its key row holds)
+        const float zd = z[u] + p.scale * row_sum16(d);
+        z[u] = z[u] == -__builtin_inff() ? z[u] : zd;
       }
     }
     float w[U];

@@ -108,3 +108,47 @@ def test_lanes_of_an_entry_agree(sd, k):
                        for _ in range(2)]).to(torch.int32)[None]
     out = sd.sparse_decode_attend(q, cache, lens, idx, sd.Sparsity(ratio=1.0, softmax_scale=1.0))
     assert torch.equal(out, out[..., :1].expand_as(out))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("layout", ["bhnd", "paged"])
+@pytest.mark.parametrize("kind", ["attend", "weighted", "fused", "forced"])
+@pytest.mark.parametrize("n", [700, 5000])
+def test_rows_outside_the_lists_are_not_read(sd, dtype, layout, kind, n):
+    # A value row (with caller lists also the key row) holding NaN at
+    # position 0, which no list keeps, changes nothing; neither does a NaN
+    # key under an entry of weight 0 whose value is finite.
+    inp = synth.make_inputs(2, seed=3, seq_lens=[n, n - 33], ncap=n, Hq=4, Hkv=2, dtype=dtype,
+                            layout=layout, ratio=9.0, n_local=40 if kind == "forced" else 0)
+    q, cache, lens = sd.cache_from_inputs(inp)
+    paged = layout == "paged"
+
+    def row(t, b, pos):
+        return t[cache.block_table[b, pos // 16], pos % 16] if paged else t[b, :, pos]
+
+    for b in range(2):  # (never selected)
+        row(cache.k, b, 0).copy_(-20 * q[b].view(2, 2, 128).float().sum(1).to(q.dtype))
+    sp = sd.sparsity_from_inputs(inp)
+    if kind in ("attend", "weighted"):
+        idx = synth.index_sets(inp, 77, seed=3, k_max=77)
+        idx[idx == 0] = 1
+        ti = torch.from_numpy(idx).cuda()
+        w = torch.rand(idx.shape, device="cuda") + 0.5
+        w[..., 5] = 0.0
+        call = ((lambda: sd.sparse_decode_attend(q, cache, lens, ti, sp)) if kind == "attend" else
+                (lambda: sd.sparse_decode_attend_weighted(q, cache, lens, ti, w, sp)))
+    else:
+        call = lambda: sd.sparse_decode_attention(q, cache, lens, sp)[0]
+    before = call()
+    for b in range(2):
+        row(cache.v, b, 0).fill_(float("nan"))
+        if kind in ("attend", "weighted"):
+            row(cache.k, b, 0).fill_(float("nan"))
+        if kind == "weighted":
+            used = set(idx[b][w[b].cpu().numpy() > 0].tolist())
+            for pos in set(idx[b, :, 5].tolist()) - used:
+                row(cache.k, b, pos).fill_(float("nan"))
+    after = call()
+    torch.cuda.synchronize()
+    assert not torch.isnan(before).any()
+    assert torch.equal(before, after)
