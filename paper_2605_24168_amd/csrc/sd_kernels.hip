@@ -2082,7 +2082,8 @@ __device__ __forceinline__ bool row_select(const float *row, uint32_t base, int 
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
           const int i = b0 + 64 * u + lane;
-          const bool pass = i <= last && v[u] >= theta;
+          // (NaNs with the sign clear rank above every number)
+          const bool pass = i <= last && (v[u] >= theta || __float_as_int(v[u]) > 0x7F800000);
           const uint64_t pm = __ballot(pass);
           const int at = cnt + lanes_below(pm);
           if (pass && at < kCap) {
@@ -2111,7 +2112,9 @@ __device__ __forceinline__ bool row_select(const float *row, uint32_t base, int 
         total += (int)rs->gt[v];
         room = room && (int)rs->gt[v] <= kCap;
       }
-      if (room && total >= k) {  // uniform: then every score >= the k-th passed
+      // Uniform: then every score from the k-th up passed.  (Not with a NaN as
+      // the threshold, which no number compares with.)
+      if (room && total >= k && th <= 0xFF800000u) {
         const RegShare cs{0, cnt, (cnt + 63) >> 6};
         uint32_t key[UMAX];
         // Buckets from the threshold to the largest sample (keys above it

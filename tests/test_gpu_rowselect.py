@@ -97,6 +97,27 @@ def test_topk_rows_of_the_lowest_nans(sd, rows, n, nans):
     np.testing.assert_array_equal(vals.cpu().numpy(), s)
 
 
+@pytest.mark.parametrize("share", [0.001, 0.03, 0.3])
+@pytest.mark.parametrize("n", [4096, 50021, 1048576])
+def test_topk_nans_rank_by_their_sign(sd, n, share):
+    # Whatever the form that a row takes, NaNs with the sign clear come above
+    # every number and the others below (fewer or more of them than k).
+    rng = np.random.default_rng(n)
+    s = rng.standard_normal((1, 2, n), dtype=np.float32)
+    at = rng.random(s.shape) < share
+    s.view(np.uint32)[at] = rng.choice(np.array([0x7FC00000, 0x7F800001, 0xFFC00000], np.uint32),
+                                       int(at.sum()))
+    idx = sd.sparse_decode_topk(torch.from_numpy(s).cuda(),
+                                torch.tensor([n], dtype=torch.int32, device="cuda"),
+                                sd.Sparsity(ratio=40.0))
+    u = s.view(np.uint32).astype(np.int64)
+    key = np.where(u >> 31, 0xFFFFFFFF - u, u + 0x80000000)
+    k = O.budget(n, 40.0, 0)
+    for r in range(2):
+        want = np.sort(np.argsort(-key[0, r], kind="stable")[:k])
+        assert np.array_equal(idx[0, r, :k].cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("L", [0, 1, 63, 16500, 50000])
 def test_topk_forced_and_short_sequences(sd, L):
     if L == 0:
