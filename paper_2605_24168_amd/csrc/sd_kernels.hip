@@ -3042,9 +3042,21 @@ constexpr float kLogitFloor = -3.402823466e38f;  // start of a running maximum (
 template <bool BF16>
 struct GatherAcc {
   float m, l, o[8];
+  float lc, oc[8];   // float32: what the additions to l and o rounded off
   float q[8];        // float32: this lane's query channels 8 col .. 8 col + 7
   uint32_t qp[4];    // bf16: the same as bf16 pairs
 };
+
+// s + c += y, c taking what the sum rounds off.  A 16-lane group adds a whole
+// share of a wave into one accumulator (16 entries of a 410-entry list, 80 of
+// a 5000-entry one on 16 waves); shorter chains on more workgroups, summed in
+// plain float32, were 1.1-1.4x closer to 64 bits.  bf16 outputs round at 2^-9
+// and are not worth the registers.
+__device__ __forceinline__ void add_exact(float &s, float &c, float y) {
+  const float t = s + y, v = t - s;
+  c += (s - (t - v)) + (y - v);
+  s = t;
+}
 
 // Sum over the 16 lanes of a DPP row, the same bits in every lane of it (each
 // step adds a pair of sums that both its lanes hold; rotations would add in
@@ -3161,6 +3173,11 @@ __device__ __forceinline__ void gather_entries(const Params &p, int b, int g, in
       st.l *= f;
 #pragma unroll
       for (int c = 0; c < 8; ++c) st.o[c] *= f;
+      if constexpr (!BF16) {
+        st.lc *= f;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) st.oc[c] *= f;
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u) w[u] = expf(z[u] - mn);
     } else {
@@ -3171,9 +3188,15 @@ __device__ __forceinline__ void gather_entries(const Params &p, int b, int g, in
     for (int u = 0; u < U; ++u) {
       float vv[8];
       unpack_raw<BF16>(v[u], vv);
-      st.l += w[u];
+      if constexpr (BF16) {
+        st.l += w[u];
 #pragma unroll
-      for (int c = 0; c < 8; ++c) st.o[c] = fmaf(w[u], vv[c], st.o[c]);
+        for (int c = 0; c < 8; ++c) st.o[c] = fmaf(w[u], vv[c], st.o[c]);
+      } else {
+        add_exact(st.l, st.lc, w[u]);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) add_exact(st.o[c], st.oc[c], w[u] * vv[c]);
+      }
     }
   };
   const int nb = (t1 - t0 + 63) >> 6;
@@ -3229,9 +3252,9 @@ __global__ __launch_bounds__(NT) void k_gather(Params p, Work w, const int32_t *
 
   GatherAcc<BF16> st;
   st.m = MODE == kGatherWeights ? 0.f : kLogitFloor;
-  st.l = 0.f;
+  st.l = st.lc = 0.f;
 #pragma unroll
-  for (int c = 0; c < 8; ++c) st.o[c] = 0.f;
+  for (int c = 0; c < 8; ++c) st.o[c] = st.oc[c] = 0.f;
   if constexpr (MODE != kGatherWeights) {
     RowRaw<BF16> qr;
     load_raw<BF16>(p.q, orow * kHeadDim, col, qr);
@@ -3263,12 +3286,12 @@ __global__ __launch_bounds__(NT) void k_gather(Params p, Work w, const int32_t *
   float m = fmaxf(st.m, __shfl_xor(st.m, 16));
   m = fmaxf(m, __shfl_xor(m, 32));
   const float f = MODE == kGatherWeights ? 1.f : expf(st.m - m);
-  float ls = st.l * f;
+  float ls = (st.l + st.lc) * f;
   ls += __shfl_xor(ls, 16);
   ls += __shfl_xor(ls, 32);
 #pragma unroll
   for (int c = 0; c < 8; ++c) {
-    float v = st.o[c] * f;
+    float v = (st.o[c] + st.oc[c]) * f;
     v += __shfl_xor(v, 16);
     v += __shfl_xor(v, 32);
     if (sub == 0) red[wv][8 * col + c] = v;

@@ -152,3 +152,27 @@ def test_rows_outside_the_lists_are_not_read(sd, dtype, layout, kind, n):
     torch.cuda.synchronize()
     assert not torch.isnan(before).any()
     assert torch.equal(before, after)
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+def test_float32_sums_do_not_drop_small_terms(sd, weighted):
+    # Every wave's share of a 5000-entry list begins with four values of 1,
+    # one per 16-lane group, and goes on with values that are lost one by one
+    # when they are added to it (just under half an ulp of 1): 78 of them per
+    # group.  Unit weights, so the exact output is the mean.  What is left to
+    # round: the sums over 4 groups, 16 waves and the quotient, 21 additions
+    # and a division, each within 2^-24 of the result (all terms positive).
+    B, n = 32, 5000
+    v = torch.full((B, 1, n, 128), 0.99 * 2.0 ** -24, device="cuda")
+    v[:, :, torch.arange(n, device="cuda") % 320 < 4] = 1.0
+    cache = sd.KVCache(k=torch.randn_like(v), v=v)
+    q = torch.zeros((B, 8, 128), device="cuda")
+    lens = torch.full((B,), n, dtype=torch.int32, device="cuda")
+    idx = torch.arange(n, dtype=torch.int32, device="cuda").expand(B, 8, n).contiguous()
+    sp = sd.Sparsity(ratio=1.0)
+    if weighted:
+        out = sd.sparse_decode_attend_weighted(q, cache, lens, idx, torch.ones_like(idx, dtype=torch.float32), sp)
+    else:
+        out = sd.sparse_decode_attend(q, cache, lens, idx, sp)
+    ref = v.double().mean(2).expand(B, 8, 128)
+    assert float(((out.double() - ref) / ref).abs().max()) <= 22 * 2.0 ** -24
