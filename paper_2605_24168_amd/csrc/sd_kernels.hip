@@ -3020,9 +3020,9 @@ __device__ __forceinline__ int64_t row_offset(const KvView &kv, int b, int g, ui
 //   kGatherWeights: the fused call's softmax weights are in sigma.
 //   kGatherScores: the fused call's scores are in sigma for the top-k part of
 //     the list; the entries around it (forced positions, draws) take their
-//     logits from their key rows.
+//     logits from their key rows (bf16).
 //   kGatherKeys: every entry's logit from its key row (caller's lists, label
-//     selection).  Entries outside [0, L_b) are skipped.
+//     selection, float32 lists with forced positions or draws).  Entries outside [0, L_b) are skipped.
 // Bound by random 256-byte gathers, so nothing waits on anything but memory:
 // a 16-lane group takes one entry at a time, its key row and value row loaded
 // side by side, the logit summed over the group's lanes and the softmax run
@@ -3789,10 +3789,20 @@ size_t select_lds_budget(bool wide) {
   return wide ? 144 * 1024 : 150 * 1024;
 }
 
+// Whether other entries share the softmax of the top-k ones: forced positions
+// or draws.
+static bool mixed_list(const Params &p) {
+  return has_forced(p.n_sink, p.n_local) || p.idx_stride > 0;
+}
+
 // Whether the attention takes the selection's scores: per-head rows on exact
 // scores (label scores are not logits; group rows need each head's own).
+// Mixed float32 lists recompute every logit: the scoring kernel's sums of 128
+// products are rougher than the gather's (one chain against a tree), which
+// float32 outputs show (4 heads of 8K, 164 kept and 160 drawn: 1.7e-7 of error
+// with recomputed logits, 2.8e-7 with scores beside them).
 static bool uses_sigma(const Params &p, const Work &w) {
-  return !p.group_shared && !p.labels && w.union_chunk == 0;
+  return !p.group_shared && !p.labels && w.union_chunk == 0 && (p.bf16 || !mixed_list(p));
 }
 
 // Rows of at most 4K scores fit the registers of 256 threads; with two or
@@ -4002,14 +4012,13 @@ static void launch_gather_nt(const Params &p, const Work &w, const int32_t *idx,
 template <bool BF16>
 static hipError_t launch_gather(const Params &p, const Work &w, const int32_t *idx, void *out,
                                 bool fused, hipStream_t st) {
-  const bool keys = !fused || p.labels;
-  const bool scores = !keys && (has_forced(p.n_sink, p.n_local) || p.idx_stride > 0);
+  const bool keys = !fused || p.labels || (!BF16 && mixed_list(p));
   const int64_t list = fused && p.idx_stride > 0 ? p.idx_stride : p.k_max;
   const int row_bytes = kHeadDim * (BF16 ? 2 : 4);
   const GatherPlan pl = gather_plan((int64_t)p.B * p.R, list, keys ? 2 * row_bytes : row_bytes);
   if (keys) launch_gather_nt<BF16, kGatherKeys>(p, w, idx, out, pl, fused, st);
-  else if (scores) launch_gather_nt<BF16, kGatherScores>(p, w, idx, out, pl, fused, st);
-  else launch_gather_nt<BF16, kGatherWeights>(p, w, idx, out, pl, fused, st);
+  else if (!mixed_list(p)) launch_gather_nt<BF16, kGatherWeights>(p, w, idx, out, pl, fused, st);
+  else if constexpr (BF16) launch_gather_nt<BF16, kGatherScores>(p, w, idx, out, pl, fused, st);
   if (pl.nsplit > 1) {
     const unsigned rows = (unsigned)(p.B * p.Hq);
     if (fused) k_merge<BF16, true><<<rows, kMergeThreads, 0, st>>>(p, w, out, pl.split);

@@ -176,3 +176,22 @@ def test_float32_sums_do_not_drop_small_terms(sd, weighted):
         out = sd.sparse_decode_attend(q, cache, lens, idx, sp)
     ref = v.double().mean(2).expand(B, 8, 128)
     assert float(((out.double() - ref) / ref).abs().max()) <= 22 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("n_sink,n_local,draws", [(128, 100, 0), (0, 0, 160), (64, 0, 33)])
+def test_float32_mixed_lists_recompute_their_logits(sd, n_sink, n_local, draws):
+    # Forced positions or draws beside the top-k: the output is, bit for bit,
+    # the unfused call's over the same list, whose logits all come from the
+    # key rows.
+    inp = synth.make_inputs(2, seed=2, B=2, N=6000, Hq=8, Hkv=4, dtype="f32", ratio=30.0,
+                            n_sink=n_sink, n_local=n_local)
+    q, cache, lens = sd.cache_from_inputs(inp)
+    sp = sd.sparsity_from_inputs(inp)
+    if draws:
+        d = torch.randint(-2**31, 2**31, (2, 8, draws), device="cuda").to(torch.int32)
+        out, idx, w = sd.sparse_decode_sampled_attention(q, cache, lens, sp, d)
+        ref = sd.sparse_decode_attend_weighted(q, cache, lens, idx, w, sp)
+    else:
+        out, idx = sd.sparse_decode_attention(q, cache, lens, sp)
+        ref = sd.sparse_decode_attend(q, cache, lens, idx, sp)
+    assert torch.equal(out, ref)
