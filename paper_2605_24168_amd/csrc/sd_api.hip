@@ -812,8 +812,15 @@ sd_status attention_impl(const sd_tensor *q, const sd_kv *K, const sd_kv *V,
   DevState *ds = nullptr;
   st = device_state(ds);
   if (st) return st;
-  if (L.total > (no_alloc ? kScratchBytes : ds->user_ws ? ds->ws_bytes : SIZE_MAX))
-    L = layout_for(s, smp ? k_list : k_max, true, sp, labels != nullptr, !smp, false);
+  // Halved waves only where there is room for their blocks.  The library's
+  // own workspace grows for them only if whole waves need it to grow as well:
+  // a graph may have been captured over it, or this call may be captured.
+  const size_t room = no_alloc ? kScratchBytes : ds->ws_bytes;
+  if (L.total > room) {
+    const Layout whole =
+        layout_for(s, smp ? k_list : k_max, true, sp, labels != nullptr, !smp, false);
+    if (no_alloc || ds->user_ws || whole.total <= room) L = whole;
+  }
   // One scoring workgroup per (chunk, sequence, KV head) on a 1-D grid.
   if ((int64_t)L.nchunk * s.B * s.Hkv > INT32_MAX) return SD_ERR_UNSUPPORTED;
   char *base = nullptr;

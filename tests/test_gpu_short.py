@@ -126,3 +126,51 @@ def test_halved_waves(sd, layout, lens, Hq, Hkv):
     for other in got[1:]:
         for x, y in zip(got[0], other):
             np.testing.assert_array_equal(x, y)
+
+
+def test_halved_waves_stay_within_the_library_workspace(sd):
+    """A call that fits the library's workspace with whole-length waves does
+    not have it grown for halved ones: a graph captured over it stays valid,
+    and the call itself can be captured.  65 chunks of 131088 keys on 8 KV
+    heads keep whole waves, 64 of 131072 would take 1 MB more than them."""
+    def make(n):
+        q = torch.randn((1, 32, 128), device="cuda").to(torch.bfloat16)
+        kv = torch.randn((2, n // 16, 16, 8, 128), device="cuda", dtype=torch.bfloat16)
+        table = torch.arange(n // 16, dtype=torch.int32, device="cuda")[None]
+        cache = sd.KVCache(k=kv[0], v=kv[1], layout="paged", block_table=table)
+        lens = torch.tensor([n], dtype=torch.int32, device="cuda")
+        idx = torch.empty((1, 32, sd.k_max_of(cache, sd.Sparsity(ratio=100.0))), dtype=torch.int32,
+                          device="cuda")
+        return q, cache, lens, torch.empty_like(q), idx
+
+    def call(args):
+        q, cache, lens, out, idx = args
+        sd.sparse_decode_attention(q, cache, lens, sd.Sparsity(ratio=100.0), out=out, idx=idx)
+
+    longer, shorter = make(131088), make(131072)
+    sizes = [sd.workspace_size(q, c, sd.Sparsity(ratio=100.0), idx) for q, c, _, _, idx in (longer, shorter)]
+    page = 2 << 20  # (allocations come in pages of 2 MB)
+    assert -(-sizes[0] // page) < -(-sizes[1] // page)
+    sd.set_workspace(None)
+    call(shorter)  # (with room of its own: halved waves)
+    torch.cuda.synchronize()
+    want = [t.clone() for t in shorter[3:]]
+    sd.set_workspace(torch.empty(256, dtype=torch.uint8, device="cuda"))
+    sd.set_workspace(None)  # (the library's workspace is given back)
+    call(longer)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    call(shorter)
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] == free
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(shorter)
+    for _ in range(3):
+        for t in shorter[3:]:
+            t.zero_()
+        call(longer)
+        graph.replay()
+        torch.cuda.synchronize()
+        for t, w in zip(shorter[3:], want):
+            assert torch.equal(t, w)
