@@ -68,34 +68,46 @@ class SdProfile(C.Structure):
 
 
 _P = C.POINTER
-_D = C.c_void_p  # a descriptor: byref of its structure, or its packed bytes (see _desc)
 lib = C.CDLL(LIB_PATH)
 lib.sparse_decode_score.restype = C.c_int
-lib.sparse_decode_score.argtypes = [_D, _D, C.c_void_p, _D, _D, C.c_void_p]
+lib.sparse_decode_score.argtypes = [_P(SdTensor), _P(SdKv), C.c_void_p, _P(SdSparsity),
+                                    _P(SdTensor), C.c_void_p]
 lib.sparse_decode_topk.restype = C.c_int
-lib.sparse_decode_topk.argtypes = [_D, C.c_void_p, _D, _D, _D, C.c_void_p]
+lib.sparse_decode_topk.argtypes = [_P(SdTensor), C.c_void_p, _P(SdSparsity), _P(SdTensor),
+                                   _P(SdTensor), C.c_void_p]
 lib.sparse_decode_attend.restype = C.c_int
-lib.sparse_decode_attend.argtypes = [_D, _D, _D, C.c_void_p, _D, _D, _D, C.c_void_p]
+lib.sparse_decode_attend.argtypes = [_P(SdTensor), _P(SdKv), _P(SdKv), C.c_void_p, _P(SdTensor),
+                                     _P(SdSparsity), _P(SdTensor), C.c_void_p]
 lib.sparse_decode_attend_weighted.restype = C.c_int
-lib.sparse_decode_attend_weighted.argtypes = [_D, _D, _D, C.c_void_p, _D, _D, _D, _D, C.c_void_p]
+lib.sparse_decode_attend_weighted.argtypes = [_P(SdTensor), _P(SdKv), _P(SdKv), C.c_void_p,
+                                              _P(SdTensor), _P(SdTensor), _P(SdSparsity),
+                                              _P(SdTensor), C.c_void_p]
 lib.sparse_decode_dense_attention.restype = C.c_int
-lib.sparse_decode_dense_attention.argtypes = [_D, _D, _D, C.c_void_p, C.c_float, _D, C.c_void_p]
+lib.sparse_decode_dense_attention.argtypes = [_P(SdTensor), _P(SdKv), _P(SdKv), C.c_void_p,
+                                              C.c_float, _P(SdTensor), C.c_void_p]
 lib.sparse_decode_dense_workspace_size.restype = C.c_int
-lib.sparse_decode_dense_workspace_size.argtypes = [_D, _D, _P(C.c_size_t)]
+lib.sparse_decode_dense_workspace_size.argtypes = [_P(SdTensor), _P(SdKv), _P(C.c_size_t)]
 lib.sparse_decode_label_attention.restype = C.c_int
-lib.sparse_decode_label_attention.argtypes = [_D, _D, _D, _D, C.c_void_p, _D, _D, _D, C.c_void_p]
+lib.sparse_decode_label_attention.argtypes = [_P(SdTensor), _P(SdKv), _P(SdKv), _P(SdLabels),
+                                              C.c_void_p, _P(SdSparsity), _P(SdTensor),
+                                              _P(SdTensor), C.c_void_p]
 lib.sparse_decode_label_score.restype = C.c_int
-lib.sparse_decode_label_score.argtypes = [_D, _D, _D, C.c_void_p, _D, _D, C.c_void_p]
+lib.sparse_decode_label_score.argtypes = [_P(SdTensor), _P(SdKv), _P(SdLabels), C.c_void_p,
+                                          _P(SdSparsity), _P(SdTensor), C.c_void_p]
 lib.sparse_decode_attention.restype = C.c_int
-lib.sparse_decode_attention.argtypes = [_D, _D, _D, C.c_void_p, _D, _D, _D, C.c_void_p]
+lib.sparse_decode_attention.argtypes = [_P(SdTensor), _P(SdKv), _P(SdKv), C.c_void_p,
+                                        _P(SdSparsity), _P(SdTensor), _P(SdTensor), C.c_void_p]
 lib.sparse_decode_attention_noalloc.restype = C.c_int
-lib.sparse_decode_attention_noalloc.argtypes = [_D, _D, _D, C.c_void_p, _D, _D, _D, C.c_void_p]
+lib.sparse_decode_attention_noalloc.argtypes = [_P(SdTensor), _P(SdKv), _P(SdKv), C.c_void_p,
+                                                _P(SdSparsity), _P(SdTensor), _P(SdTensor),
+                                                C.c_void_p]
 lib.sparse_decode_workspace_size.restype = C.c_int
-lib.sparse_decode_workspace_size.argtypes = [_D, _D, _D, _D, _P(C.c_size_t)]
+lib.sparse_decode_workspace_size.argtypes = [_P(SdTensor), _P(SdKv), _P(SdSparsity), _P(SdTensor),
+                                             _P(C.c_size_t)]
 lib.sparse_decode_set_workspace.restype = C.c_int
 lib.sparse_decode_set_workspace.argtypes = [C.c_void_p, C.c_size_t]
 lib.sparse_decode_budget.restype = C.c_int64
-lib.sparse_decode_budget.argtypes = [C.c_int64, _D]
+lib.sparse_decode_budget.argtypes = [C.c_int64, _P(SdSparsity)]
 lib.sparse_decode_set_profiling.restype = C.c_int
 lib.sparse_decode_set_profiling.argtypes = [C.c_int32]
 lib.sparse_decode_last_profile.restype = C.c_int
@@ -105,12 +117,24 @@ lib.sparse_decode_profile_mean.argtypes = [_P(SdProfile), _P(C.c_int32)]
 lib.sparse_decode_set_debug.restype = C.c_int
 lib.sparse_decode_set_debug.argtypes = [C.c_int32]
 lib.sparse_decode_sampled_attention.restype = C.c_int
-lib.sparse_decode_sampled_attention.argtypes = [_D, _D, _D, C.c_void_p, _D, _D, _D, _D, _D,
-                                                C.c_void_p]
+lib.sparse_decode_sampled_attention.argtypes = [_P(SdTensor), _P(SdKv), _P(SdKv), C.c_void_p,
+                                                _P(SdSparsity), _P(SdTensor), _P(SdTensor),
+                                                _P(SdTensor), _P(SdTensor), C.c_void_p]
 lib.sparse_decode_read_probe.restype = C.c_int
 lib.sparse_decode_read_probe.argtypes = [C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p]
 lib.sparse_decode_status_string.restype = C.c_char_p
 lib.sparse_decode_status_string.argtypes = [C.c_int]
+
+# The same entry points for the calls below, which pass descriptors as packed
+# bytes (see _desc); `lib` takes the structures and checks their types.
+_raw = C.CDLL(LIB_PATH)
+for _name in ("score", "topk", "attend", "attend_weighted", "dense_attention",
+              "dense_workspace_size", "label_attention", "label_score", "attention",
+              "attention_noalloc", "workspace_size", "budget", "sampled_attention"):
+    _f, _g = getattr(lib, f"sparse_decode_{_name}"), getattr(_raw, f"sparse_decode_{_name}")
+    _g.restype = _f.restype
+    _g.argtypes = [C.c_void_p if _t in (_P(SdTensor), _P(SdKv), _P(SdSparsity), _P(SdLabels)) else _t
+                   for _t in _f.argtypes]
 
 
 class SparseDecodeError(RuntimeError):
@@ -301,7 +325,7 @@ def _stream(stream) -> Optional[int]:
 
 def budget(L: int, sparsity: Sparsity) -> int:
     """k for a sequence of L positions under the ratio rule."""
-    return int(lib.sparse_decode_budget(int(L), _sparsity_desc(sparsity)))
+    return int(_raw.sparse_decode_budget(int(L), _sparsity_desc(sparsity)))
 
 
 def rows_of(q: torch.Tensor, cache: KVCache, sparsity: Sparsity) -> int:
@@ -320,7 +344,7 @@ def sparse_decode_score(q, cache: KVCache, seq_lens, sparsity: Sparsity, scores=
                              dtype=torch.float32, device=q.device)
     sp, kq, kk = _sparsity_desc(sparsity), _desc(q, "q"), _kv_desc(cache, "k")
     ks = _desc(scores, "scores")
-    _check(lib.sparse_decode_score(kq, kk, seq_lens.data_ptr(), sp, ks, _stream(stream)),
+    _check(_raw.sparse_decode_score(kq, kk, seq_lens.data_ptr(), sp, ks, _stream(stream)),
            "sparse_decode_score")
     return scores
 
@@ -338,7 +362,7 @@ def sparse_decode_topk(scores, seq_lens, sparsity: Sparsity, k_max: Optional[int
         vals = torch.empty(idx.shape, dtype=torch.float32, device=scores.device)
     sp, cs, ci = _sparsity_desc(sparsity), _desc(scores, "scores"), _desc(idx, "idx")
     cv = _desc(vals, "vals") if vals is not None else None
-    _check(lib.sparse_decode_topk(cs, seq_lens.data_ptr(), sp, ci, cv, _stream(stream)),
+    _check(_raw.sparse_decode_topk(cs, seq_lens.data_ptr(), sp, ci, cv, _stream(stream)),
            "sparse_decode_topk")
     return (idx, vals) if vals is not None else idx
 
@@ -352,8 +376,8 @@ def sparse_decode_attend(q, cache: KVCache, seq_lens, idx, sparsity: Sparsity, o
     sp = _sparsity_desc(sparsity)
     cq, (kk, kv) = _desc(q, "q"), _kv_desc(cache, "k", "v")
     ci, co = _desc(idx, "idx"), _desc(out, "out")
-    _check(lib.sparse_decode_attend(cq, kk, kv, seq_lens.data_ptr(), ci, sp, co,
-                                    _stream(stream)),
+    _check(_raw.sparse_decode_attend(cq, kk, kv, seq_lens.data_ptr(), ci, sp, co,
+                                     _stream(stream)),
            "sparse_decode_attend")
     return out
 
@@ -369,8 +393,8 @@ def sparse_decode_attend_weighted(q, cache: KVCache, seq_lens, idx, weights, spa
     sp = _sparsity_desc(sparsity)
     cq, (kk, kv) = _desc(q, "q"), _kv_desc(cache, "k", "v")
     ci, cw, co = _desc(idx, "idx"), _desc(weights, "weights"), _desc(out, "out")
-    _check(lib.sparse_decode_attend_weighted(cq, kk, kv, seq_lens.data_ptr(), ci, cw, sp, co,
-                                             _stream(stream)),
+    _check(_raw.sparse_decode_attend_weighted(cq, kk, kv, seq_lens.data_ptr(), ci, cw, sp, co,
+                                              _stream(stream)),
            "sparse_decode_attend_weighted")
     return out
 
@@ -382,8 +406,8 @@ def sparse_decode_dense_attention(q, cache: KVCache, seq_lens, softmax_scale: fl
     if out is None:
         out = torch.empty_like(q)
     cq, (kk, kv), co = _desc(q, "q"), _kv_desc(cache, "k", "v"), _desc(out, "out")
-    _check(lib.sparse_decode_dense_attention(cq, kk, kv,
-                                             seq_lens.data_ptr(), float(softmax_scale),
+    _check(_raw.sparse_decode_dense_attention(cq, kk, kv,
+                                              seq_lens.data_ptr(), float(softmax_scale),
                                              co, _stream(stream)),
            "sparse_decode_dense_attention")
     return out
@@ -392,7 +416,7 @@ def sparse_decode_dense_attention(q, cache: KVCache, seq_lens, softmax_scale: fl
 def dense_workspace_size(q, cache: KVCache) -> int:
     n = C.c_size_t(0)
     cq, kk = _desc(q, "q"), _kv_desc(cache, "k")
-    _check(lib.sparse_decode_dense_workspace_size(cq, kk, C.byref(n)),
+    _check(_raw.sparse_decode_dense_workspace_size(cq, kk, C.byref(n)),
            "sparse_decode_dense_workspace_size")
     return int(n.value)
 
@@ -411,8 +435,8 @@ def sparse_decode_attention(q, cache: KVCache, seq_lens, sparsity: Sparsity, out
     sp = _sparsity_desc(sparsity)
     cq, (kk, kv) = _desc(q, "q"), _kv_desc(cache, "k", "v")
     co, ci = _desc(out, "out"), _desc(idx, "idx")
-    _check(lib.sparse_decode_attention(cq, kk, kv, seq_lens.data_ptr(), sp, co, ci,
-                                       _stream(stream)),
+    _check(_raw.sparse_decode_attention(cq, kk, kv, seq_lens.data_ptr(), sp, co, ci,
+                                        _stream(stream)),
            "sparse_decode_attention")
     return out, idx
 
@@ -428,8 +452,8 @@ def sparse_decode_attention_noalloc(q, cache: KVCache, seq_lens, sparsity: Spars
     sp = _sparsity_desc(sparsity)
     cq, (kk, kv) = _desc(q, "q"), _kv_desc(cache, "k", "v")
     co, ci = _desc(out, "out"), _desc(idx, "idx")
-    _check(lib.sparse_decode_attention_noalloc(cq, kk, kv, seq_lens.data_ptr(), sp, co, ci,
-                                               _stream(stream)),
+    _check(_raw.sparse_decode_attention_noalloc(cq, kk, kv, seq_lens.data_ptr(), sp, co, ci,
+                                                _stream(stream)),
            "sparse_decode_attention_noalloc")
     return out, idx
 
@@ -449,8 +473,8 @@ def sparse_decode_label_attention(q, cache: KVCache, labels: Labels, seq_lens, s
     sp, lab = _sparsity_desc(sparsity), _labels_desc(labels)
     cq, (kk, kv) = _desc(q, "q"), _kv_desc(cache, "k", "v")
     co, ci = _desc(out, "out"), _desc(idx, "idx")
-    _check(lib.sparse_decode_label_attention(cq, kk, kv, lab, seq_lens.data_ptr(), sp, co, ci,
-                                             _stream(stream)),
+    _check(_raw.sparse_decode_label_attention(cq, kk, kv, lab, seq_lens.data_ptr(), sp, co, ci,
+                                              _stream(stream)),
            "sparse_decode_label_attention")
     return out, idx
 
@@ -464,8 +488,8 @@ def sparse_decode_label_score(q, cache: KVCache, labels: Labels, seq_lens, spars
                              dtype=torch.float32, device=q.device)
     sp, lab = _sparsity_desc(sparsity), _labels_desc(labels)
     cq, kk, ks = _desc(q, "q"), _kv_desc(cache, "k"), _desc(scores, "scores")
-    _check(lib.sparse_decode_label_score(cq, kk, lab, seq_lens.data_ptr(), sp, ks,
-                                         _stream(stream)), "sparse_decode_label_score")
+    _check(_raw.sparse_decode_label_score(cq, kk, lab, seq_lens.data_ptr(), sp, ks,
+                                          _stream(stream)), "sparse_decode_label_score")
     return scores
 
 
@@ -473,8 +497,8 @@ def workspace_size(q, cache: KVCache, sparsity: Sparsity, idx) -> int:
     n = C.c_size_t(0)
     sp, cq, kk = _sparsity_desc(sparsity), _desc(q, "q"), _kv_desc(cache, "k")
     ci = _desc(idx, "idx")
-    _check(lib.sparse_decode_workspace_size(cq, kk, sp, ci,
-                                            C.byref(n)), "sparse_decode_workspace_size")
+    _check(_raw.sparse_decode_workspace_size(cq, kk, sp, ci,
+                                             C.byref(n)), "sparse_decode_workspace_size")
     return int(n.value)
 
 
@@ -536,8 +560,8 @@ def sparse_decode_sampled_attention(q, cache: KVCache, seq_lens, sparsity: Spars
     cq, (kk, kv) = _desc(q, "q"), _kv_desc(cache, "k", "v")
     cd, co, ci, cw = _desc(draws, "draws"), _desc(out, "out"), _desc(idx, "idx"), \
         _desc(weights, "weights")
-    _check(lib.sparse_decode_sampled_attention(cq, kk, kv, seq_lens.data_ptr(), sp, cd, co, ci, cw,
-                                               _stream(stream)),
+    _check(_raw.sparse_decode_sampled_attention(cq, kk, kv, seq_lens.data_ptr(), sp, cd, co, ci, cw,
+                                                _stream(stream)),
            "sparse_decode_sampled_attention")
     return out, idx, weights
 

@@ -1,5 +1,7 @@
 """The packed descriptors that the binding passes are, byte for byte, the
 ctypes structures of the C ABI."""
+import ctypes as C
+
 import pytest
 import torch
 
@@ -39,3 +41,14 @@ def test_packed_tensors_and_caches():
 def test_packed_sparsity(kw):
     a, b = bytes(sd.Sparsity(**kw).c()), sd._sparsity_desc(sd.Sparsity(**kw))
     assert a[:20] == b[:20] and a[24:] == b[24:]  # (bytes 20-23: padding)
+
+
+def test_the_library_takes_its_structures_and_no_others():
+    sp = sd.Sparsity(ratio=10.0).c()
+    assert sd.lib.sparse_decode_budget(1000, sp) == 100  # (an instance, as its pointer)
+    assert sd.lib.sparse_decode_budget(1000, C.byref(sp)) == 100
+    assert sd.lib.sparse_decode_budget(1000, C.pointer(sp)) == 100
+    assert sd.budget(1000, sd.Sparsity(ratio=10.0)) == 100
+    for other in (C.byref(sd.SdTensor()), bytes(sp), 4096):
+        with pytest.raises(C.ArgumentError):
+            sd.lib.sparse_decode_budget(1000, other)
