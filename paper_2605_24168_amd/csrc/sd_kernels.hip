@@ -2082,8 +2082,8 @@ __device__ __forceinline__ bool row_select(const float *row, uint32_t base, int 
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
           const int i = b0 + 64 * u + lane;
-          // (NaNs with the sign clear rank above every number)
-          const bool pass = i <= last && (v[u] >= theta || __float_as_int(v[u]) > 0x7F800000);
+          // (NaNs pass too: those with the sign clear rank above every number)
+          const bool pass = i <= last && !(v[u] < theta);
           const uint64_t pm = __ballot(pass);
           const int at = cnt + lanes_below(pm);
           if (pass && at < kCap) {
@@ -2105,36 +2105,41 @@ __device__ __forceinline__ bool row_select(const float *row, uint32_t base, int 
       cnt = __builtin_amdgcn_readfirstlane(cnt);
       if (lane == 0) rs->gt[wv] = (uint32_t)cnt;
       __syncthreads();
-      int total = 0;
       bool room = true;
 #pragma unroll
-      for (int v = 0; v < NW; ++v) {
-        total += (int)rs->gt[v];
-        room = room && (int)rs->gt[v] <= kCap;
-      }
-      // Uniform: then every score from the k-th up passed.  (Not with a NaN as
-      // the threshold, which no number compares with.)
-      if (room && total >= k && th <= 0xFF800000u) {
+      for (int v = 0; v < NW; ++v) room = room && (int)rs->gt[v] <= kCap;
+      if (room) {  // uniform
         const RegShare cs{0, cnt, (cnt + 63) >> 6};
         uint32_t key[UMAX];
         // Buckets from the threshold to the largest sample (keys above it
         // join the top one).
         const KeyBuckets kb = KeyBuckets::make(th, smax - th);
         uint32_t cmx = 0u;
+        int items = 0;  // (without the NaNs that rank below the threshold)
         unroll_slots<UMAX>(cs.U, [&](auto uc) {
           constexpr int u = decltype(uc)::value;
-          const bool in = 64 * u + lane < cnt;
-          key[u] = in ? row_key(cand[64 * u + lane]) : 0u;
+          const uint32_t x = 64 * u + lane < cnt ? row_key(cand[64 * u + lane]) : 0u;
+          const bool in = x >= th;
+          key[u] = in ? x : 0u;
           cmx = key[u] > cmx ? key[u] : cmx;
+          items += __popcll(__ballot(in));
           wave_hist(hist, kb.of(key[u]), in);
         });
         cmx = wave_max_u32(cmx);
-        if (lane == 0) rs->wmax[wv] = cmx;
+        if (lane == 0) {
+          rs->wmax[wv] = cmx;
+          rs->eq[wv] = (uint32_t)items;
+        }
         __syncthreads();
-        reg_select<NT, UMAX>(key, cs, k, kb, hist, hist2, ss, bs, rs,
-                             [&](int i) { return base + (uint32_t)(sh.i0 + (int)off[i]); }, irow,
-                             vrow, weights, row_max(), scale);
-        return true;
+        int total = 0;
+#pragma unroll
+        for (int v = 0; v < NW; ++v) total += (int)rs->eq[v];
+        if (total >= k) {  // uniform: then every score from the k-th up passed
+          reg_select<NT, UMAX>(key, cs, k, kb, hist, hist2, ss, bs, rs,
+                               [&](int i) { return base + (uint32_t)(sh.i0 + (int)off[i]); }, irow,
+                               vrow, weights, row_max(), scale);
+          return true;
+        }
       }
       __syncthreads();  // (the counts are read before the LDS is reused)
     }
