@@ -1113,8 +1113,9 @@ struct ScoreInit {
 // waves) x groups, 1-D.  The waves of a workgroup take consecutive runs of
 // one head, a head's slab swept in order; in the paged layout heads go
 // fastest and, with a multiple of 4 of them, the waves take four heads of
-// the same run (a position's heads are adjacent in a page).  fill: positions
-// past the sequence get -inf.
+// the same run (a position's heads are adjacent in a page).  blocks: the
+// longest run, a sequence of the full capacity's.  fill: positions past the
+// sequence get -inf.
 template <bool PAGED, bool GRP, int NR>
 __global__ __launch_bounds__(kBlock) void k_score_keys(Params p, float *dst, int64_t ld, int blocks,
                                                        int runs, int fill, ScoreInit init) {
@@ -1148,7 +1149,16 @@ __global__ __launch_bounds__(kBlock) void k_score_keys(Params p, float *dst, int
     b = wid / (rw * p.Hkv);
   }
   if (run >= runs) return;  // (per wave: no block barriers)
-  const int L = seq_len(p, b), nkeys = blocks * kScoreBlock;
+  // A sequence that fills only 1/f of the cache takes runs 1/f as long, so that
+  // as many waves have one (a fused call over 172K of 688K positions, 8 KV
+  // heads, with the capacity's runs on 1024 waves: 268 us, now 214).  By
+  // whole factors only: just under the capacity, even runs would all be long
+  // ones, one more than the chip holds (31 x 8 heads of 19523 of 19536
+  // positions: 215 -> 229 us).  Not where the tail is filled: the waves past
+  // the sequence are the ones that fill it.
+  const int L = seq_len(p, b);
+  const int f = fill || L == 0 ? 1 : (int)(p.ncap / L);
+  const int nkeys = (blocks + f - 1) / f * kScoreBlock;
   const int64_t j0 = (int64_t)run * nkeys;
   score_run<PAGED, GRP, NR>(p, dst, ld, b, g, j0, nkeys, L, sl[wv]);
   const int64_t end = j0 + nkeys < p.ncap ? j0 + nkeys : p.ncap;

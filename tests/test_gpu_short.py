@@ -174,3 +174,46 @@ def test_halved_waves_stay_within_the_library_workspace(sd):
         torch.cuda.synchronize()
         for t, w in zip(shorter[3:], want):
             assert torch.equal(t, w)
+
+
+@pytest.mark.parametrize("layout", ["bhnd", "paged"])
+@pytest.mark.parametrize("Hq,Hkv,shared", [(4, 4, False), (8, 2, False), (12, 4, True)])
+@pytest.mark.parametrize("ncap", [1040, 20000, 400000])
+def test_sequences_shorter_than_the_cache(sd, layout, Hq, Hkv, shared, ncap):
+    """Calls scored in full (debug flag 1) over ragged sequences in a longer
+    cache keep what each sequence keeps in a cache of its own length (there
+    the rows are the same bit for bit, only their lists' padding differs)."""
+    lens = [min(n, ncap) for n in (0, 1, 63, 65, 1039, 4100, 19999)]
+    inp = synth.make_inputs(2, seed=6, seq_lens=lens, ncap=max(lens), Hq=Hq, Hkv=Hkv,
+                            layout=layout, group_shared=shared)
+    q, cache, sl = sd.cache_from_inputs(inp)
+    sp = sd.sparsity_from_inputs(inp)
+    if layout == "paged":
+        wide = torch.full((len(lens), ncap // 16), -1, dtype=torch.int32, device="cuda")
+        wide[:, :cache.block_table.shape[1]] = cache.block_table
+        big = sd.KVCache(k=cache.k, v=cache.v, layout=layout, block_table=wide)
+    else:
+        k, v = (torch.zeros((len(lens), Hkv, ncap, 128), dtype=torch.bfloat16, device="cuda")
+                for _ in range(2))
+        k[:, :, :max(lens)], v[:, :, :max(lens)] = cache.k, cache.v
+        big = sd.KVCache(k=k, v=v)
+    sd.set_debug(1)
+    try:
+        out, idx = sd.sparse_decode_attention(q, big, sl, sp)
+        for b, L in enumerate(lens):
+            k_b = sd.budget(L, sp)
+            assert (idx[b, :, k_b:] == -1).all()
+            if L == 0:
+                assert (out[b] == 0).all()
+                continue
+            if layout == "paged":
+                own = sd.KVCache(k=cache.k, v=cache.v, layout=layout,
+                                 block_table=cache.block_table[b:b + 1, :-(-L // 16)].contiguous())
+            else:
+                own = sd.KVCache(k=cache.k[b:b + 1, :, :L].contiguous(), v=cache.v[b:b + 1, :, :L].contiguous())
+            ref, ridx = sd.sparse_decode_attention(q[b:b + 1].contiguous(), own, sl[b:b + 1], sp)
+            assert torch.equal(idx[b, :, :k_b], ridx[0, :, :k_b])
+            ok, worst, _ = P.out_errors(P.to_host(out[b]), P.to_host(ref[0]), "bf16")
+            assert ok, worst
+    finally:
+        sd.set_debug(0)
