@@ -1151,7 +1151,7 @@ __global__ __launch_bounds__(kBlock) void k_score_keys(Params p, float *dst, int
   if (run >= runs) return;  // (per wave: no block barriers)
   // A sequence that fills only 1/f of the cache takes runs 1/f as long, so that
   // as many waves have one (a fused call over 172K of 688K positions, 8 KV
-  // heads, with the capacity's runs on 1024 waves: 268 us, now 214).  By
+  // heads, with the capacity's runs on 1024 waves: 268 us, now 216).  By
   // whole factors only: just under the capacity, even runs would all be long
   // ones, one more than the chip holds (31 x 8 heads of 19523 of 19536
   // positions: 215 -> 229 us).  Not where the tail is filled: the waves past
@@ -3030,8 +3030,8 @@ __device__ __forceinline__ int64_t row_offset(const KvView &kv, int b, int g, ui
 
 // ---------------------------------------------------------------------------
 // Gather-attend of per-head rows.  grid = (splits, rows), workgroup s of row
-// (b, r), query head r, takes entries [s*split, +split) of its list, each
-// wave a contiguous share of them.
+// (b, r), query head r, takes the s-th of gridDim.x even parts of its list
+// (gather_row_split), each wave a contiguous share of it.
 //   kGatherWeights: the fused call's softmax weights are in sigma.
 //   kGatherScores: the fused call's scores are in sigma for the top-k part of
 //     the list; the entries around it (forced positions, draws) take their
@@ -3241,9 +3241,21 @@ __device__ __forceinline__ void gather_entries(const Params &p, int b, int g, in
   }
 }
 
+constexpr int kGatherSplitMin = 256;  // fewest entries of a 256-thread workgroup of a split row
+
+// Entries per workgroup of a row of n entries over at most nsplit workgroups:
+// the row's own list in even parts, so that rows shorter than the lists that
+// the call has room for (ragged lengths, a cache of more capacity) still take
+// all of them.
+__device__ __forceinline__ int gather_row_split(int n, int nsplit) {
+  if (nsplit <= 1) return n;
+  const int even = ((n + nsplit - 1) / nsplit + 63) & ~63;
+  return even > kGatherSplitMin ? even : kGatherSplitMin;
+}
+
 template <bool BF16, int MODE, int NT>
 __global__ __launch_bounds__(NT) void k_gather(Params p, Work w, const int32_t *idx, void *out,
-                                               int split, int fused) {
+                                               int fused) {
   constexpr int NW = NT / 64;
   __shared__ float red[NW][kHeadDim], red_m[NW], red_l[NW];
   const int s = blockIdx.x;
@@ -3251,7 +3263,8 @@ __global__ __launch_bounds__(NT) void k_gather(Params p, Work w, const int32_t *
   const int b = row / p.R, r = row % p.R, g = r / p.G;
   const int L = seq_len(p, b);
   const int n_list = attend_list_len(p, b, L, fused);
-  const int nsp = (n_list + split - 1) / split;
+  const int split = gather_row_split(n_list, (int)gridDim.x);
+  const int nsp = split > 0 ? (n_list + split - 1) / split : 0;
   const int tid = threadIdx.x, l = lane_id(), col = l & 15, sub = l >> 4, wv = wave_id();
   const int64_t orow = (int64_t)b * p.Hq + r;
   if (n_list == 0 || L == 0) {  // nothing kept: zero output
@@ -3698,15 +3711,20 @@ __global__ __launch_bounds__(kBlock) void k_attend(Params p, Work w, const int32
 }
 
 // Log-sum-exp merge of split partials: grid = B*Hq output rows, blocks of
-// kMergeThreads.  Rows that fit one split were written by k_attend.
+// kMergeThreads.  Rows that fit one split were written by k_attend or
+// k_gather.  split: entries per split of group rows; 0: rows of k_gather over
+// at most `nsplit` workgroups.
 template <bool BF16, bool FUSED>
-__global__ __launch_bounds__(kMergeThreads) void k_merge(Params p, Work w, void *out, int split) {
+__global__ __launch_bounds__(kMergeThreads) void k_merge(Params p, Work w, void *out, int split,
+                                                         int nsplit) {
   __shared__ MergeShared sh;
   const int bh = blockIdx.x, b = bh / p.Hq;
   const int L = seq_len(p, b);
   const int n_list = w.union_chunk ? L : attend_list_len(p, b, L, FUSED);
+  if (n_list == 0 || L == 0) return;  // (written directly)
+  if (split == 0) split = gather_row_split(n_list, nsplit);
   const int nsp = (n_list + split - 1) / split;
-  if (nsp <= 1 || L == 0) return;  // written directly by k_attend
+  if (nsp <= 1) return;
   const float v = merge_partials(w.part + (int64_t)bh * w.nsplit * kPartStride, nsp, sh);
   if (threadIdx.x < kHeadDim) store_out<BF16>(out, (int64_t)bh * kHeadDim + threadIdx.x, v);
 }
@@ -3970,7 +3988,7 @@ int attend_split(const Params &p, int k_max_positions, bool fused) {
   return (int)split;
 }
 
-// Per-head rows: threads per workgroup and entries per workgroup.  About
+// Per-head rows: threads per workgroup and workgroups per row.  About
 // kGatherWaves waves in all, 16 per CU (registers allow no more beside key
 // rows), each with at least 64 entries.  A row of up to 16 waves is one
 // workgroup and needs no merge (a launch of 4-5 us), and so does a row that
@@ -3981,7 +3999,7 @@ int attend_split(const Params &p, int k_max_positions, bool fused) {
 constexpr int kGatherWaves = 4096;
 constexpr int64_t kGatherWhole = 420 * 1024;
 struct GatherPlan {
-  int nt, split, nsplit;
+  int nt, nsplit;
 };
 static GatherPlan gather_plan(int64_t rows, int64_t k, int entry_bytes) {
   k = k > 0 ? k : 1;
@@ -3989,11 +4007,11 @@ static GatherPlan gather_plan(int64_t rows, int64_t k, int entry_bytes) {
   const int64_t blocks = (k + 63) / 64;
   waves = waves < blocks ? waves : blocks;
   waves = waves > 1 ? waves : 1;
-  GatherPlan pl{256, (int)((k + 63) / 64 * 64), 1};
+  GatherPlan pl{256, 1};
   if (waves > 16 && k * entry_bytes > kGatherWhole) {
     pl.nsplit = (int)(waves / kWaves);
-    pl.split = (int)(((k + pl.nsplit - 1) / pl.nsplit + 63) / 64 * 64);
-    pl.nsplit = (int)((k + pl.split - 1) / pl.split);
+    const int64_t split = ((k + pl.nsplit - 1) / pl.nsplit + 63) / 64 * 64;
+    pl.nsplit = (int)((k + split - 1) / split);
   } else {
     // (two workgroups of 512 threads fit a CU, one of 1024)
     pl.nt = waves > 8 && rows <= 256 ? 1024 : (waves > 4 ? 512 : 256);
@@ -4019,9 +4037,9 @@ static void launch_gather_nt(const Params &p, const Work &w, const int32_t *idx,
                              const GatherPlan &pl, bool fused, hipStream_t st) {
   const dim3 grid(pl.nsplit, p.B * p.R);
   const int f = fused ? 1 : 0;
-  if (pl.nt == 256) k_gather<BF16, MODE, 256><<<grid, 256, 0, st>>>(p, w, idx, out, pl.split, f);
-  else if (pl.nt == 512) k_gather<BF16, MODE, 512><<<grid, 512, 0, st>>>(p, w, idx, out, pl.split, f);
-  else k_gather<BF16, MODE, 1024><<<grid, 1024, 0, st>>>(p, w, idx, out, pl.split, f);
+  if (pl.nt == 256) k_gather<BF16, MODE, 256><<<grid, 256, 0, st>>>(p, w, idx, out, f);
+  else if (pl.nt == 512) k_gather<BF16, MODE, 512><<<grid, 512, 0, st>>>(p, w, idx, out, f);
+  else k_gather<BF16, MODE, 1024><<<grid, 1024, 0, st>>>(p, w, idx, out, f);
 }
 
 template <bool BF16>
@@ -4031,13 +4049,14 @@ static hipError_t launch_gather(const Params &p, const Work &w, const int32_t *i
   const int64_t list = fused && p.idx_stride > 0 ? p.idx_stride : p.k_max;
   const int row_bytes = kHeadDim * (BF16 ? 2 : 4);
   const GatherPlan pl = gather_plan((int64_t)p.B * p.R, list, keys ? 2 * row_bytes : row_bytes);
+  if (pl.nsplit > w.nsplit) return hipErrorInvalidValue;  // (the partials' room)
   if (keys) launch_gather_nt<BF16, kGatherKeys>(p, w, idx, out, pl, fused, st);
   else if (!mixed_list(p)) launch_gather_nt<BF16, kGatherWeights>(p, w, idx, out, pl, fused, st);
   else if constexpr (BF16) launch_gather_nt<BF16, kGatherScores>(p, w, idx, out, pl, fused, st);
   if (pl.nsplit > 1) {
     const unsigned rows = (unsigned)(p.B * p.Hq);
-    if (fused) k_merge<BF16, true><<<rows, kMergeThreads, 0, st>>>(p, w, out, pl.split);
-    else k_merge<BF16, false><<<rows, kMergeThreads, 0, st>>>(p, w, out, pl.split);
+    if (fused) k_merge<BF16, true><<<rows, kMergeThreads, 0, st>>>(p, w, out, 0, pl.nsplit);
+    else k_merge<BF16, false><<<rows, kMergeThreads, 0, st>>>(p, w, out, 0, pl.nsplit);
   }
   return hipGetLastError();
 }
@@ -4066,7 +4085,7 @@ hipError_t launch_attend(const Params &p, const Work &w, const int32_t *idx, voi
     const dim3 grid(nsplit, p.B * p.Hkv);
     if (p.G <= 4) k_attend<true, true, true, 4><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
     else k_attend<true, true, true><<<grid, kBlock, lds, st>>>(p, w, idx, out, split);
-    if (nsplit > 1) k_merge<true, true><<<(unsigned)(p.B * p.Hq), kMergeThreads, 0, st>>>(p, w, out, split);
+    if (nsplit > 1) k_merge<true, true><<<(unsigned)(p.B * p.Hq), kMergeThreads, 0, st>>>(p, w, out, split, 0);
     return hipGetLastError();
   }
   if (!p.group_shared)
@@ -4087,11 +4106,11 @@ hipError_t launch_attend(const Params &p, const Work &w, const int32_t *idx, voi
   if (nsplit > 1) {
     const unsigned rows = (unsigned)(p.B * p.Hq);
     if (p.bf16) {
-      if (fused) k_merge<true, true><<<rows, kMergeThreads, 0, st>>>(p, w, out, split);
-      else k_merge<true, false><<<rows, kMergeThreads, 0, st>>>(p, w, out, split);
+      if (fused) k_merge<true, true><<<rows, kMergeThreads, 0, st>>>(p, w, out, split, 0);
+      else k_merge<true, false><<<rows, kMergeThreads, 0, st>>>(p, w, out, split, 0);
     } else {
-      if (fused) k_merge<false, true><<<rows, kMergeThreads, 0, st>>>(p, w, out, split);
-      else k_merge<false, false><<<rows, kMergeThreads, 0, st>>>(p, w, out, split);
+      if (fused) k_merge<false, true><<<rows, kMergeThreads, 0, st>>>(p, w, out, split, 0);
+      else k_merge<false, false><<<rows, kMergeThreads, 0, st>>>(p, w, out, split, 0);
     }
   }
   return hipGetLastError();
