@@ -399,6 +399,7 @@ Layout layout_for(const Shape &s, int64_t k_max, bool fused, const sd_sparsity *
   shape_only.R = s.R;
   shape_only.G = s.G;
   shape_only.group_shared = group_shared;
+  shape_only.bf16 = s.bf16;
   shape_only.k_max = (int32_t)k_max;
   shape_only.n_sink = sp->n_sink;
   shape_only.n_local = sp->n_local;

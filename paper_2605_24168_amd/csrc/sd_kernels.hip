@@ -3241,16 +3241,22 @@ __device__ __forceinline__ void gather_entries(const Params &p, int b, int g, in
   }
 }
 
-constexpr int kGatherSplitMin = 256;  // fewest entries of a 256-thread workgroup of a split row
+// Fewest entries worth a wave.  A wave has 16 bf16 or 8 float32 entries (of
+// twice the bytes) in flight at a time: with 64 each, float32 lists of a few
+// hundred entries were chains of 8 round trips on a few waves (20 rows of 995
+// entries with their keys: 28 us in the former kernel, 46 us so).
+constexpr int gather_wave_min(bool bf16) { return bf16 ? 64 : 32; }
 
 // Entries per workgroup of a row of n entries over at most nsplit workgroups:
 // the row's own list in even parts, so that rows shorter than the lists that
 // the call has room for (ragged lengths, a cache of more capacity) still take
 // all of them.
+template <bool BF16>
 __device__ __forceinline__ int gather_row_split(int n, int nsplit) {
+  constexpr int least = kWaves * gather_wave_min(BF16);
   if (nsplit <= 1) return n;
   const int even = ((n + nsplit - 1) / nsplit + 63) & ~63;
-  return even > kGatherSplitMin ? even : kGatherSplitMin;
+  return even > least ? even : least;
 }
 
 template <bool BF16, int MODE, int NT>
@@ -3263,7 +3269,7 @@ __global__ __launch_bounds__(NT) void k_gather(Params p, Work w, const int32_t *
   const int b = row / p.R, r = row % p.R, g = r / p.G;
   const int L = seq_len(p, b);
   const int n_list = attend_list_len(p, b, L, fused);
-  const int split = gather_row_split(n_list, (int)gridDim.x);
+  const int split = gather_row_split<BF16>(n_list, (int)gridDim.x);
   const int nsp = split > 0 ? (n_list + split - 1) / split : 0;
   const int tid = threadIdx.x, l = lane_id(), col = l & 15, sub = l >> 4, wv = wave_id();
   const int64_t orow = (int64_t)b * p.Hq + r;
@@ -3722,7 +3728,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(Params p, Work w, void 
   const int L = seq_len(p, b);
   const int n_list = w.union_chunk ? L : attend_list_len(p, b, L, FUSED);
   if (n_list == 0 || L == 0) return;  // (written directly)
-  if (split == 0) split = gather_row_split(n_list, nsplit);
+  if (split == 0) split = gather_row_split<BF16>(n_list, nsplit);
   const int nsp = (n_list + split - 1) / split;
   if (nsp <= 1) return;
   const float v = merge_partials(w.part + (int64_t)bh * w.nsplit * kPartStride, nsp, sh);
@@ -3990,21 +3996,21 @@ int attend_split(const Params &p, int k_max_positions, bool fused) {
 
 // Per-head rows: threads per workgroup and workgroups per row.  About
 // kGatherWaves waves in all, 16 per CU (registers allow no more beside key
-// rows), each with at least 64 entries.  A row of up to 16 waves is one
+// rows), each with at least gather_wave_min entries.  A row of up to 16 waves is one
 // workgroup and needs no merge (a launch of 4-5 us), and so does a row that
 // one workgroup gathers in that time anyway (kGatherWhole bytes).  Other
 // rows are split into 256-thread workgroups, so that all are resident at once
 // (96 rows on 288 workgroups of 1024 threads, one per CU, left most of the
-// chip idle in the second round: 70 against 63 us).
+// chip idle after the first ones ended: 70 against 63 us).
 constexpr int kGatherWaves = 4096;
 constexpr int64_t kGatherWhole = 420 * 1024;
 struct GatherPlan {
   int nt, nsplit;
 };
-static GatherPlan gather_plan(int64_t rows, int64_t k, int entry_bytes) {
+static GatherPlan gather_plan(int64_t rows, int64_t k, int entry_bytes, bool bf16) {
   k = k > 0 ? k : 1;
   int64_t waves = kGatherWaves / rows;
-  const int64_t blocks = (k + 63) / 64;
+  const int64_t blocks = (k + gather_wave_min(bf16) - 1) / gather_wave_min(bf16);
   waves = waves < blocks ? waves : blocks;
   waves = waves > 1 ? waves : 1;
   GatherPlan pl{256, 1};
@@ -4022,7 +4028,7 @@ static GatherPlan gather_plan(int64_t rows, int64_t k, int entry_bytes) {
 int attend_nsplit(const Params &p) {
   // The largest split count of any call of this shape.
   const int64_t k_max = p.k_max > 0 ? p.k_max : 1;
-  if (!p.group_shared) return gather_plan((int64_t)p.B * p.R, k_max, 1 << 20).nsplit;
+  if (!p.group_shared) return gather_plan((int64_t)p.B * p.R, k_max, 1 << 20, p.bf16 != 0).nsplit;
   int most = 1;
   for (int fused = 0; fused < 2; ++fused) {
     const int split = attend_split(p, p.k_max, fused != 0);
@@ -4048,7 +4054,7 @@ static hipError_t launch_gather(const Params &p, const Work &w, const int32_t *i
   const bool keys = !fused || p.labels || (!BF16 && mixed_list(p));
   const int64_t list = fused && p.idx_stride > 0 ? p.idx_stride : p.k_max;
   const int row_bytes = kHeadDim * (BF16 ? 2 : 4);
-  const GatherPlan pl = gather_plan((int64_t)p.B * p.R, list, keys ? 2 * row_bytes : row_bytes);
+  const GatherPlan pl = gather_plan((int64_t)p.B * p.R, list, keys ? 2 * row_bytes : row_bytes, BF16);
   if (pl.nsplit > w.nsplit) return hipErrorInvalidValue;  // (the partials' room)
   if (keys) launch_gather_nt<BF16, kGatherKeys>(p, w, idx, out, pl, fused, st);
   else if (!mixed_list(p)) launch_gather_nt<BF16, kGatherWeights>(p, w, idx, out, pl, fused, st);
