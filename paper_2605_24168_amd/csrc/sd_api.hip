@@ -381,7 +381,7 @@ Layout layout_for(const Shape &s, int64_t k_max, bool fused, const sd_sparsity *
   // selection's per-chunk tables.
   const int64_t qchunks = (s.ncap + L.wave_keys - 1) / L.wave_keys;
   const bool quad = s.paged && s.Hkv % sd::kWaves == 0 && qchunks <= 8192;
-  if (halve && fused && !labels) {
+  if (halve && fused && s.bf16 && !labels) {  // (float32 keys are not streamed)
     const int64_t heads = (int64_t)s.B * (quad ? s.Hkv / sd::kWaves : s.Hkv);
     const int waves = quad ? 1 : sd::kWaves;
     auto chunks = [&](int wk) { return (s.ncap + (int64_t)waves * wk - 1) / (waves * wk); };

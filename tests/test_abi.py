@@ -291,6 +291,21 @@ def test_workspace_size_and_status_strings(sd):
         assert text in sd.lib.sparse_decode_status_string(code).decode()
 
 
+def test_float32_workspace_does_not_pay_for_stream_waves(sd):
+    # A longer cache needs no less: 64 chunks of 2048 keys on 8 paged KV heads
+    # would halve the waves of a bf16 stream, 65 do not.
+    sizes = []
+    for pages in (8192, 8193):
+        q, K = tensor(sd, (1, 32, 128), sd.SD_F32), paged(sd, P=8193, max_pages=pages, dtype=sd.SD_F32)
+        idx = tensor(sd, (1, 32, 1400), sd.SD_I32)
+        n = C.c_size_t(0)
+        assert sd.lib.sparse_decode_workspace_size(C.byref(q), C.byref(K), C.byref(sparsity(sd, 100.0)),
+                                                   C.byref(idx), C.byref(n)) == 0
+        sizes.append(n.value)
+    assert sizes[0] <= sizes[1]
+
+
+
 def test_binding_refuses_host_tensors(sd):
     import torch
     q = torch.zeros((1, 8, 128), dtype=torch.bfloat16)
