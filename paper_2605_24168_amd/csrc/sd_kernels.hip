@@ -4155,14 +4155,24 @@ hipError_t launch_score_dense(const Params &p, float *scores, hipStream_t st) {
   // Workgroups of 8192 keys, or as many as make about 2048 in all, each wave
   // with a tile of its own: float32 keys and labels are read a tile at a time
   // (4096 float32 keys of one head in one workgroup: 290 us; 2 x 8K x 2 heads
-  // 1.17 ms).
+  // 1.17 ms).  Labels: at most 2048, and none but the workgroups of 8192 keys
+  // where these fill the chip's 512 or 1024 places to 80% or more (two heads
+  // to a group or more, whose scoring is bound by issue: 54 groups of 67.5K,
+  // G = 2, 486 workgroups: 49 us, as 1998: 58, as 2052: 64; 240 groups of
+  // 8.9K, G = 5, 480: 38, as 1920: 53).
   const int64_t groups = (int64_t)p.B * p.Hkv, tiles = cdiv(p.ncap, kTile);
-  int64_t want = (2048 + groups - 1) / groups;
+  const int64_t whole = cdiv(p.ncap, kDenseChunk);
+  int64_t want = p.labels ? 2048 / groups : (2048 + groups - 1) / groups;
+  if (p.labels && p.G >= 2 && tiles >= 64 * kWaves * whole) {
+    const int64_t wgs = whole * groups;
+    if ((wgs > 400 && wgs <= 512) || (wgs > 900 && wgs <= 1024)) want = whole;
+  }
   want = want < (int64_t)cdiv(tiles, kWaves) ? want : (int64_t)cdiv(tiles, kWaves);
-  int64_t parts = cdiv(p.ncap, kDenseChunk);
-  parts = parts > want ? parts : want;
+  const int64_t parts = whole > want ? whole : want;
   const dim3 grid((unsigned)parts, p.B * p.Hkv);
-  const bool pipe = dense_pipelined(p, (int)parts);
+  // (label waves of up to 24 tiles are faster one tile at a time, more of them
+  // resident: 376 groups of 5K at 15.8 tiles a wave: 59 against 27 us)
+  const bool pipe = dense_pipelined(p, (int)parts) && !(p.labels && tiles < 24 * kWaves * parts);
   if (p.labels) {
     if (pipe) k_score_dense<true, true, true><<<grid, kBlock, 0, st>>>(p, scores, p.ncap);
     else k_score_dense<true, true, false><<<grid, kBlock, 0, st>>>(p, scores, p.ncap);

@@ -249,3 +249,32 @@ def test_label_indexer_selection_in_pieces(sd, name):
     np.testing.assert_array_equal(idx, idx2)
     np.testing.assert_array_equal(out, out2)
     check(inp, ch, lab, out, idx, f"labels in pieces {name}")
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n", [
+    (9, 12, 6, 67536),   # 486 workgroups of 8192 keys, kept
+    (30, 40, 8, 8880), (47, 32, 8, 5040),  # whole rounds; 15.8 tiles a wave, one at a time
+    (2, 8, 1, 100000), (3, 3, 3, 17),      # many workgroups to a group; two tiles
+])
+def test_label_scores_do_not_depend_on_the_split(sd, B, Hq, Hkv, n):
+    # Each sequence's scores are, bit for bit, those of a call of its own,
+    # which is cut into other workgroups.  (Pages are shared: 64 in all.)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    npg = -(-n // 16)
+    k = torch.randn((64, 16, Hkv, 128), generator=g, device="cuda").to(torch.bfloat16)
+    t = torch.randn((64, Hkv, 16, 8), generator=g, device="cuda").to(torch.bfloat16)
+    table = torch.randint(64, (B, npg), generator=g, device="cuda").to(torch.int32)
+    q = torch.randn((B, Hq, 128), generator=g, device="cuda").to(torch.bfloat16)
+    lens = torch.tensor([n - 7 * b for b in range(B)], dtype=torch.int32, device="cuda").clamp(min=0)
+    ch = torch.arange(8, dtype=torch.int32, device="cuda").repeat(Hkv, 1)
+    sp = sd.Sparsity(ratio=10.0)
+
+    def scores(b0, b1):
+        cache = sd.KVCache(k=k, v=k, layout="paged", block_table=table[b0:b1].contiguous())
+        return sd.sparse_decode_label_score(q[b0:b1].contiguous(), cache, sd.Labels(t=t, channels=ch),
+                                            lens[b0:b1].contiguous(), sp)
+
+    whole = scores(0, B)
+    for b in {0, B // 2, B - 1}:
+        assert torch.equal(whole[b], scores(b, b + 1)[0])
+        assert torch.isneginf(whole[b, :, int(lens[b]):]).all()
