@@ -308,6 +308,10 @@ int psel_parts_for(const Shape &s, int nchunk) {
 }
 
 constexpr int64_t kManyCandidates = 48 * 1024;
+// Full score rows selected by one workgroup each: up to this many positions,
+// or at least this many rows (see attention_impl).
+constexpr int64_t kOneWorkgroupKeys = 256 * 1024;
+constexpr int64_t kOneWorkgroupRows = 16;
 constexpr int64_t kPieceCandidates = 8 * 1024;  // fewest candidates per row worth the pieces
 constexpr int64_t kPieceItems = 3 * 1024;       // most expected candidates per piece
 
@@ -848,11 +852,17 @@ sd_status attention_impl(const sd_tensor *q, const sd_kv *K, const sd_kv *V,
   const bool one_pass = sd::row_selects(full_plan.hi - full_plan.lo, full_plan.kh);
   if (one_pass && !(g_debug.load() & (16 | 32 | 64)) && full_scores_pay(s, labels != nullptr))
     w.force_repair = 1;
-  // Those rows select over several workgroups each when they are few and
-  // one workgroup would need several passes over a row (one pass by one
-  // workgroup takes 15-25 us at 32K-128K scores; the pieces' eight kernels
-  // more than that whatever the row).
-  if (w.force_repair && !one_pass) w.dsel_parts = L.dsel_parts;
+  // Those rows select over several workgroups each (eight short kernels) when
+  // one workgroup would need several passes over a row, or when they are few
+  // and so long that its one pass takes more than that.  One sequence, every
+  // row from full scores at 200x, us for the call by one workgroup per row and
+  // by pieces: 8 rows 34 / 53 at 64K positions, 48 / 59 at 128K, 79 / 82 at
+  // 256K, 105 / 101 at 384K, 130 / 119 at 512K; 1 row 73 / 73 at 256K, 120 /
+  // 103 at 512K, 206 / 163 at 1M; 16 rows (of two sequences) 207 / 219 at 512K;
+  // 32 rows 167 / 206 at 512K, 295 / 359 at 1M.
+  const bool one_workgroup =
+      one_pass && (s.ncap <= kOneWorkgroupKeys || (int64_t)s.B * s.R >= kOneWorkgroupRows);
+  if (w.force_repair && !one_workgroup) w.dsel_parts = L.dsel_parts;
   sd::Params p = make_params(q, K, V, seq_lens, sp, s, k_max);
   if (labels) {
     p.labels = (const uint16_t *)labels->t.data;

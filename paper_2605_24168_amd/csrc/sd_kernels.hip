@@ -1968,16 +1968,33 @@ constexpr size_t row_select_lds(int64_t n) {
 }
 
 // Samples of a long row of n scores for a top-k of k, and the rank r among
-// them that gives the threshold; 0: its candidates would not fit.
+// them that gives the threshold; 0: its candidates would not fit 4/5 of the
+// room.  The fewest samples that also leave a wave's share room for 3.5
+// deviations of the threshold (1 / sqrt(r)) and 2.5 of the share's own count,
+// else the most that fit.  sure: whether the former.  (With 4/5 of the room
+// alone, some of 32 rows took the radix passes in calls of 393K scores at 40x,
+// 694 us where 156 do, and with 3 deviations in calls of 524K at 40x, 927 us
+// where the pieces take 232; 131K scores at 10x pay 4 us for more samples.)
 constexpr int kRowSampleMax = 8192;
-__host__ __device__ inline int row_samples(int64_t n, int64_t k, int &r) {
+__host__ __device__ inline int row_samples(int64_t n, int64_t k, int &r, bool *sure = nullptr) {
+  if (sure) *sure = false;
   if (n > 16LL * kRowShareMax) return 0;
+  constexpr float room = 64.f * kRowCands;  // candidates of a wave
+  int fits = 0, rank = 0;
   for (int m = kSampleMax; m <= kRowSampleMax && m < n; m *= 4) {
     const int64_t rr = pilot_rank(k, m, n);
     r = (int)(rr < kPilotMinRank ? kPilotMinRank : rr);
-    if (5LL * r * n <= 4LL * m * 1024 * kRowCands) return m;
+    if (5LL * r * n > 4LL * m * 1024 * kRowCands) continue;
+    const float per = (float)r * (float)n / (16.f * (float)m);
+    if (per * (1.f + 3.5f / sqrtf((float)r)) + 2.5f * sqrtf(per) <= room) {
+      if (sure) *sure = true;
+      return m;
+    }
+    fits = m;
+    rank = r;
   }
-  return 0;
+  r = rank;
+  return fits;
 }
 
 // Top k of the n scores at `row`, positions base, base + 1, ...: entries
@@ -3853,7 +3870,9 @@ static bool row_narrow(int64_t rows, int64_t n) {
 
 bool row_selects(int64_t n, int64_t k) {
   int r;
-  return n <= kRowDirectMax || row_samples(n, k, r) > 0;
+  bool sure;
+  row_samples(n, k, r, &sure);
+  return n <= kRowDirectMax || sure;
 }
 
 hipError_t launch_select_candidates(const Params &p, const Work &w, int32_t *idx, int lds_cap,

@@ -75,7 +75,8 @@ def check(sd, s, L, ratio, n_sink=0, n_local=0):
     (513, 4096, 20.0), (513, 4097, 20.0),        # 256-thread rows, and past them
     (2, 16384, 20.0), (2, 16385, 20.0),          # in registers, and past them
     (2, 50021, 9.0), (2, 50021, 1.5),            # filtered; too many candidates
-    (2, 131072, 11.0), (1, 1048576, 100.0), (1, 1048577, 100.0),  # 8192 samples; 16-bit offsets end
+    (2, 131072, 11.0), (3, 393216, 40.0),        # 8192 samples
+    (1, 1048576, 100.0), (1, 1048577, 100.0),    # at 4/5 of the room; 16-bit offsets end
 ])
 def test_topk_rows(sd, kind, rows, n, ratio):
     check(sd, rows_of_kind(kind, rows, n), n, ratio)
@@ -141,3 +142,24 @@ def test_fused_rows_from_full_scores(sd, n, ratio):
                                           k_max=O.k_max_for(inp))
     torch.cuda.synchronize()
     check_fused(inp, P.to_host(out), idx.cpu().numpy(), label=f"{n} at {ratio}x")
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n", [
+    (1, 3, 3, 262144), (1, 3, 3, 262160),   # one workgroup per row; pieces
+    (1, 15, 3, 300000), (1, 16, 2, 300000),  # pieces; one workgroup, enough rows
+])
+def test_long_rows_by_one_workgroup_or_in_pieces(sd, B, Hq, Hkv, n):
+    """Every row from its full scores (debug flag 1): the lists are those of
+    the stand-alone selection over the stand-alone scores."""
+    g = torch.Generator(device="cuda").manual_seed(n + Hq)
+    k = torch.randn((B, Hkv, n, 128), generator=g, device="cuda").to(torch.bfloat16)
+    q = torch.randn((B, Hq, 128), generator=g, device="cuda").to(torch.bfloat16)
+    cache, sp = sd.KVCache(k=k, v=k), sd.Sparsity(ratio=60.0)
+    lens = torch.full((B,), n - 3, dtype=torch.int32, device="cuda")
+    sd.set_debug(1)
+    try:
+        idx = sd.sparse_decode_attention(q, cache, lens, sp)[1]
+    finally:
+        sd.set_debug(0)
+    scores = sd.sparse_decode_score(q, cache, lens, sp)
+    assert torch.equal(idx, sd.sparse_decode_topk(scores, lens, sp))
