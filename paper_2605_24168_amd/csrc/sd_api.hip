@@ -346,16 +346,35 @@ bool all_rows_fall_back(const Shape &s, const sd_sparsity *sp, int wave_keys, in
 // scores, written and read back (labels 1.45), 8 us per 64K scores of a row
 // (one workgroup reads it), and 9 us per GB of keys (labels 35), their stream
 // being the slower one.  Least squares over 434 (labels 382) shapes measured
-// both ways: 1-32 sequences of 4K-128K keys, 1-32 KV heads, both layouts, at
-// 20x; 5 us (labels 3) are kept as a margin.  At the sides: 32 heads on 8 KV
-// heads, paged, 8K keys: 68 against 28 us for one sequence, 111 against 95
-// for 16; 64K keys: 75 against 68 us for one, 153 against 164 for 4.
-bool full_scores_pay(const Shape &s, bool labels) {
+// both ways; 5 us (labels 3) are kept as a margin.  At the sides: 32 heads on
+// 8 KV heads, paged, 8K keys: 68 against 28 us for one sequence, 111 against
+// 95 for 16; 64K keys: 75 against 68 us for one, 153 against 164 for 4.
+//
+// From 6M scores on, near the 8M (32 MB) that the caches hold, the latencies
+// count little and the fit alone picked calls that lose up to 15% (16 sequences
+// of 16K on 8 of 32 heads at 200x: 128 against 147 us).  A second condition
+// there weighs what grows with the size: a group costs the candidate path its
+// samples, scattered in the paged layout, and the kept entries their way
+// through the candidates.  Beyond 12M scores only contexts near the samples'
+// own length gain (64 sequences of 4K on 32 KV heads at 20x: 616 against 442
+// us, of 8K on 8 of 32 heads: 299 against 331).
+//
+// Checked on shapes of other sizes (1-128 sequences of 1.5K-80K positions, 1-16
+// heads to each of 1-8 KV heads, 4x-150x, per head and shared): of 2678 picked
+// calls 32 lose over 3%, at most 8% where they take over 50 us; of 570 with
+// labels 16, at most 13% (8 us).  Lengths are the cache's capacity, all that
+// the host knows: short sequences in a long cache stay on the candidate path.
+bool full_scores_pay(const Shape &s, int64_t k, bool labels) {
   const double scores = 1e-6 * s.B * s.R * (double)s.ncap;
   const double key_gb = 256e-9 * s.B * s.Hkv * (double)s.ncap;
   const double len = (double)s.ncap / 65536.0;
+  const double groups = s.B * (double)s.Hkv / 128.0;
   if (labels) return 1.45 * scores + 7.0 * len + 35.0 * key_gb < 11.0;
-  return 1.2 * scores + 8.0 * len + 9.0 * key_gb - 5.0 * (s.B * s.Hkv / 128.0) < 13.0;
+  if (1.2 * scores + 8.0 * len + 9.0 * key_gb - 5.0 * groups >= 13.0) return false;
+  if (scores < 6.0) return true;
+  if (scores >= 12.0 && s.ncap > 4608) return false;
+  const double kept = 1e-6 * s.B * s.R * (double)k;
+  return 1.7 * scores + 17.0 * key_gb < (s.paged ? 11.5 : 9.0) * groups + 9.0 * kept + 3.0;
 }
 
 // Fewest units of the persistent stream (a chunk of one KV head, or of four
@@ -850,7 +869,7 @@ sd_status attention_impl(const sd_tensor *q, const sd_kv *K, const sd_kv *V,
                    sp->k_override ? k_max : sd::budget_rule(s.ncap, sp->ratio, sp->k_rounding),
                    (int)k_max);
   const bool one_pass = sd::row_selects(full_plan.hi - full_plan.lo, full_plan.kh);
-  if (one_pass && !(g_debug.load() & (16 | 32 | 64)) && full_scores_pay(s, labels != nullptr))
+  if (one_pass && !(g_debug.load() & (16 | 32 | 64)) && full_scores_pay(s, full_plan.kh, labels != nullptr))
     w.force_repair = 1;
   // Those rows select over several workgroups each (eight short kernels) when
   // one workgroup would need several passes over a row, or when they are few
