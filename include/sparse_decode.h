@@ -120,11 +120,13 @@ typedef struct {
 typedef struct {
   float pilot_ms;      /* threshold estimation from a strided sample of keys      */
   float score_ms;      /* full scoring stream + candidate filter                  */
-  float select_ms;     /* exact top-k over the candidates                         */
-  float repair_ms;     /* exact fallback for rows whose candidates were not enough */
+  float select_ms;     /* exact top-k over the candidates or full scores          */
+  float repair_ms;     /* full scores: of rows whose candidates were not enough, or
+                          of every row of a call that goes without candidates
+                          (short contexts, float32, low sparsity)                 */
   float attend_ms;     /* gather of the selected value rows + softmax + merge     */
   float total_ms;
-  int32_t repaired_rows; /* rows that took the exact fallback                     */
+  int32_t repaired_rows; /* rows selected from their full scores, in either case  */
   int32_t valid;         /* 1 if the fields above are filled                      */
 } sd_profile;
 
@@ -299,9 +301,10 @@ int64_t sparse_decode_budget(int64_t L, const sd_sparsity *sparsity);
 /* Profiling: while enabled, sparse_decode_attention records HIP events
  * between its stages on the call's stream (a ring of 64 calls per device;
  * enabling again starts a new series).  enable = 1 records every stage;
- * enable = 2 times only the scoring kernel, with events attached to its own
- * dispatch (the profile then holds score_ms alone; nothing is added to the
- * stream between kernels).  sparse_decode_last_profile waits for
+ * enable = 2 times only the scoring kernel (the profile then holds score_ms
+ * alone): the scoring stream with events attached to its own dispatch, so
+ * that nothing is added between kernels; the full scores of a call that goes
+ * without a stream (repaired_rows counts all its rows) between two events.  sparse_decode_last_profile waits for
  * the most recent call's events and fills `out`; sparse_decode_profile_mean
  * averages the stage times of the series' last min(n, 64) calls and stores
  * that count in *n_calls (repaired_rows is the last call's). */
@@ -318,7 +321,8 @@ sd_status sparse_decode_profile_mean(sd_profile *out, int32_t *n_calls);
  * fewer than 256 rows, no group-deduplicated attention), overriding its
  * cost rule (rows expecting 8K candidates or more); flags & 64, and 16 and
  * 32 too, keep calls on the candidate path whose rows the cost rule for
- * short contexts would select from their full scores.  0 restores normal. */
+ * short contexts would select from their full scores (it goes by the cache's
+ * capacity: the sequences' lengths are device memory).  0 restores normal. */
 sd_status sparse_decode_set_debug(int32_t flags);
 
 /* Measurement helper, not a step of the method: one streaming read of

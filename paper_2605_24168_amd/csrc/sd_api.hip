@@ -959,16 +959,16 @@ sd_status attention_impl(const sd_tensor *q, const sd_kv *K, const sd_kv *V,
   // (the pilot's thresholds and flags serve only the scoring stream)
   if (e == hipSuccess && !w.force_repair) e = sd::launch_pilot(p, w, stream_h);
   if (e == hipSuccess) e = mark(1);
-  // Level 2 times the scoring kernel alone, with events attached to its
-  // dispatch (recorded back to back when the kernel does not run).
+  // Level 2 times the scoring kernel alone: the stream with events attached to
+  // its dispatch, the full scores of a call without one between two events.
   const bool streams = s.ncap > 0 && !w.force_repair;
   if (e == hipSuccess && prof_level == 2 && !streams) e = hipEventRecord(ev[1], stream_h);
-  if (e == hipSuccess && prof_level == 2 && !streams) e = hipEventRecord(ev[2], stream_h);
   if (e == hipSuccess && streams)
     e = prof_level == 2 ? sd::launch_score_stream(p, w, stream_h, ev[1], ev[2])
                         : sd::launch_score_stream(p, w, stream_h);
   if (e == hipSuccess) e = mark(2);
   if (e == hipSuccess && s.ncap > 0) e = sd::launch_repair(p, w, stream_h);
+  if (e == hipSuccess && prof_level == 2 && !streams) e = hipEventRecord(ev[2], stream_h);
   if (e == hipSuccess) e = mark(3);
   if (e == hipSuccess) e = sd::launch_dense_select(p, w, idx_ptr, stream_h);
   if (e == hipSuccess) e = sd::launch_select_candidates(p, w, idx_ptr, lds_cap, wide, stream_h);
@@ -1059,7 +1059,7 @@ sd_status sparse_decode_label_score(const sd_tensor *q, const sd_kv *K, const sd
 namespace {
 
 // Stage times of ring slot `slot` (its events must be complete).  A slot
-// recorded at level 2 has only the scoring-stream time (t[1]); the other
+// recorded at level 2 has only the scoring kernel's time (t[1]); the other
 // entries are 0.
 sd_status read_slot(DevState &ds, int slot, float t[6]) {
   hipEvent_t *ev = ds.ev[slot];

@@ -217,3 +217,24 @@ def test_sequences_shorter_than_the_cache(sd, layout, Hq, Hkv, shared, ncap):
             assert ok, worst
     finally:
         sd.set_debug(0)
+
+
+@pytest.mark.parametrize("n", [16384, 131072])  # full scores; the stream
+def test_the_scoring_kernel_that_runs_is_timed(sd, n):
+    """Profiling level 2: no scoring kernel reads its keys in less than the
+    time that they take at 8 TB/s, whichever one a call takes."""
+    kv = torch.randn((2, 2, 8, n, 128), device="cuda", dtype=torch.bfloat16)
+    q = torch.randn((2, 32, 128), device="cuda").to(torch.bfloat16)
+    cache = sd.KVCache(k=kv[0], v=kv[1])
+    lens = torch.full((2,), n, dtype=torch.int32, device="cuda")
+    sd.set_profiling(2)
+    try:
+        for _ in range(3):
+            sd.sparse_decode_attention(q, cache, lens, sd.Sparsity(ratio=50.0))
+        torch.cuda.synchronize()
+        prof = sd.profile_mean()
+    finally:
+        sd.set_profiling(False)
+    assert prof["valid"] == 1 and prof["calls"] == 3
+    assert prof["repaired_rows"] == (64 if n == 16384 else 0)
+    assert prof["score_ms"] >= kv[0].numel() * 2 / 8e12 * 1e3
