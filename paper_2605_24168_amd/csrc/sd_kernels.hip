@@ -1157,8 +1157,11 @@ __global__ __launch_bounds__(kBlock) void k_score_keys(Params p, float *dst, int
   // positions: 215 -> 229 us).  Not where the tail is filled: the waves past
   // the sequence are the ones that fill it.
   const int L = seq_len(p, b);
-  const int f = fill || L == 0 ? 1 : (int)(p.ncap / L);
-  const int nkeys = (blocks + f - 1) / f * kScoreBlock;
+  int nkeys = blocks * kScoreBlock;
+  if (!fill && L > 0 && 2 * (int64_t)L <= p.ncap) {  // (capacities have 24 bits)
+    const uint32_t f = (uint32_t)p.ncap / (uint32_t)L;
+    nkeys = (int)(((uint32_t)blocks + f - 1) / f) * kScoreBlock;
+  }
   const int64_t j0 = (int64_t)run * nkeys;
   score_run<PAGED, GRP, NR>(p, dst, ld, b, g, j0, nkeys, L, sl[wv]);
   const int64_t end = j0 + nkeys < p.ncap ? j0 + nkeys : p.ncap;
@@ -3082,8 +3085,8 @@ struct GatherAcc {
 // s + c += y, c taking what the sum rounds off.  A 16-lane group adds a whole
 // share of a wave into one accumulator (16 entries of a 410-entry list, 80 of
 // a 5000-entry one on 16 waves); shorter chains on more workgroups, summed in
-// plain float32, were 1.1-1.4x closer to 64 bits.  bf16 outputs round at 2^-9
-// and are not worth the registers.
+// plain float32, were 1.1-1.4x closer to 64 bits.  (y: the sum of a batch's two
+// entries.)  bf16 outputs round at 2^-9 and are not worth the registers.
 __device__ __forceinline__ void add_exact(float &s, float &c, float y) {
   const float t = s + y, v = t - s;
   c += (s - (t - v)) + (y - v);
@@ -3216,6 +3219,7 @@ __device__ __forceinline__ void gather_entries(const Params &p, int b, int g, in
 #pragma unroll
       for (int u = 0; u < U; ++u) w[u] = z[u];
     }
+    float y[8], yl = 0.f;  // float32: the batch's sums
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       float vv[8];
@@ -3225,10 +3229,15 @@ __device__ __forceinline__ void gather_entries(const Params &p, int b, int g, in
 #pragma unroll
         for (int c = 0; c < 8; ++c) st.o[c] = fmaf(w[u], vv[c], st.o[c]);
       } else {
-        add_exact(st.l, st.lc, w[u]);
+        yl += w[u];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) add_exact(st.o[c], st.oc[c], w[u] * vv[c]);
+        for (int c = 0; c < 8; ++c) y[c] = u == 0 ? w[u] * vv[c] : fmaf(w[u], vv[c], y[c]);
       }
+    }
+    if constexpr (!BF16) {
+      add_exact(st.l, st.lc, yl);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) add_exact(st.o[c], st.oc[c], y[c]);
     }
   };
   const int nb = (t1 - t0 + 63) >> 6;
@@ -4028,17 +4037,22 @@ struct GatherPlan {
 };
 static GatherPlan gather_plan(int64_t rows, int64_t k, int entry_bytes, bool bf16) {
   k = k > 0 ? k : 1;
-  int64_t waves = kGatherWaves / rows;
-  const int64_t blocks = (k + gather_wave_min(bf16) - 1) / gather_wave_min(bf16);
-  waves = waves < blocks ? waves : blocks;
-  waves = waves > 1 ? waves : 1;
+  auto waves_of = [&](int64_t entries) {  // of at least so many entries each
+    const int64_t most = kGatherWaves / rows, blocks = (k + entries - 1) / entries;
+    const int64_t w = most < blocks ? most : blocks;
+    return w > 1 ? w : 1;
+  };
+  int64_t waves = waves_of(gather_wave_min(bf16));
   GatherPlan pl{256, 1};
   if (waves > 16 && k * entry_bytes > kGatherWhole) {
     pl.nsplit = (int)(waves / kWaves);
     const int64_t split = ((k + pl.nsplit - 1) / pl.nsplit + 63) / 64 * 64;
     pl.nsplit = (int)((k + split - 1) / split);
   } else {
-    // (two workgroups of 512 threads fit a CU, one of 1024)
+    // (two workgroups of 512 threads fit a CU, one of 1024; the sum over more
+    // waves costs a short float32 row what the shorter shares save: one row of
+    // 410 on 7 waves 4.9 us, on 13 6.5 us)
+    waves = waves_of(64);
     pl.nt = waves > 8 && rows <= 256 ? 1024 : (waves > 4 ? 512 : 256);
   }
   return pl;

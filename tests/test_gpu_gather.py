@@ -158,10 +158,11 @@ def test_rows_outside_the_lists_are_not_read(sd, dtype, layout, kind, n):
 def test_float32_sums_do_not_drop_small_terms(sd, weighted):
     # Every wave's share of a 5000-entry list begins with four values of 1,
     # one per 16-lane group, and goes on with values that are lost one by one
-    # when they are added to it (just under half an ulp of 1): 78 of them per
+    # when they are added to it (just under half an ulp of 1): 79 of them per
     # group.  Unit weights, so the exact output is the mean.  What is left to
-    # round: the sums over 4 groups, 16 waves and the quotient, 21 additions
-    # and a division, each within 2^-24 of the result (all terms positive).
+    # round: a batch's pair of entries, the sums over 4 groups and 16 waves and
+    # the quotient, 20 additions and a division, each within 2^-24 of the
+    # result (all terms positive).
     B, n = 32, 5000
     v = torch.full((B, 1, n, 128), 0.99 * 2.0 ** -24, device="cuda")
     v[:, :, torch.arange(n, device="cuda") % 320 < 4] = 1.0
