@@ -87,12 +87,13 @@ def test_short_context_rule(sd, kind, layout, Hq, Hkv, lens, ncap):
 @pytest.mark.parametrize("layout,lens,Hq,Hkv", [
     ("paged", [32768], 32, 8),          # 32 units of 2048-key waves, halved twice
     ("paged", [65536, 1025], 8, 4),     # 64 units: at 512 keys a whole round
-    ("paged", [1024, 1023, 513], 12, 6),  # one head per workgroup, under a chunk
+    ("paged", [10000, 8193, 513], 12, 6),  # one head per workgroup: 36 units, four waves a chunk
     ("bhnd", [131071], 8, 2),           # 32 units, the last chunk one key short
 ])
 def test_halved_waves(sd, layout, lens, Hq, Hkv):
     """Calls of few stream units run shorter waves where their workspace has
-    room; both give the lists of the full-score path."""
+    room; both give the lists of the stand-alone selection over the
+    stand-alone scores, and the same outputs."""
     inp = synth.make_inputs(2, seed=5, seq_lens=lens, ncap=max(lens), Hq=Hq, Hkv=Hkv,
                             layout=layout, ratio=40.0)
     q, cache, sl = sd.cache_from_inputs(inp)
@@ -100,32 +101,40 @@ def test_halved_waves(sd, layout, lens, Hq, Hkv):
     kmax = O.k_max_for(inp)
     idx = torch.empty((inp.B, Hq, kmax), dtype=torch.int32, device="cuda")
     buf = torch.empty(sd.workspace_size(q, cache, sp, idx), dtype=torch.uint8, device="cuda")
+    sd.set_debug(CANDIDATES)
 
-    def call(flags, room):
-        sd.set_debug(flags)
+    def call(room):
+        """(out, idx, end of what was written to the workspace)"""
+        buf.fill_(0xA5)
         sd.set_workspace(buf[:room])
         try:
             out = [P.to_host(t) for t in sd.sparse_decode_attention(q, cache, sl, sp, k_max=kmax)]
             torch.cuda.synchronize()
-            return out
+            return *out, int((buf != 0xA5).nonzero().max())
         finally:
             sd.set_workspace(None)
-            sd.set_debug(0)
 
-    # The smallest workspace that is taken (too small ones launch nothing):
-    # the one of whole-length waves.
-    lo, hi = 0, buf.numel() // 256
-    while hi - lo > 1:
-        mid = (lo + hi) // 2
-        try:
-            call(CANDIDATES, 256 * mid)
-            hi = mid
-        except sd.SparseDecodeError:
-            lo = mid
-    got = [call(0, buf.numel()), call(CANDIDATES, buf.numel()), call(CANDIDATES, 256 * hi)]
-    for other in got[1:]:
-        for x, y in zip(got[0], other):
-            np.testing.assert_array_equal(x, y)
+    try:
+        # The smallest workspace that is taken (too small ones launch
+        # nothing): the one of whole-length waves.
+        lo, hi = 0, buf.numel() // 256
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            try:
+                call(256 * mid)
+                hi = mid
+            except sd.SparseDecodeError:
+                lo = mid
+        halved, whole = call(buf.numel()), call(256 * hi)
+    finally:
+        sd.set_debug(0)
+    # (two layouts: whole-length waves write less of the workspace)
+    assert whole[2] < 256 * hi <= buf.numel() and whole[2] < halved[2], (whole[2], halved[2])
+    scores = sd.sparse_decode_score(q, cache, sl, sp)
+    want = P.to_host(sd.sparse_decode_topk(scores, sl, sp, k_max=kmax))
+    for got in (halved, whole):
+        np.testing.assert_array_equal(got[1], want)
+    np.testing.assert_array_equal(halved[0], whole[0])
 
 
 def test_halved_waves_stay_within_the_library_workspace(sd):
