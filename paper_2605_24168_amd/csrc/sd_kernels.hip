@@ -3,7 +3,11 @@
 // time; Table 1: k = N/S per query head; per-query, per-head, token-level
 // sparsity under GQA).
 //
-// Fused pipeline for one decode step, all on the caller's stream:
+// Fused pipeline for one decode step, all on the caller's stream.  Short
+// contexts, float32 caches and calls whose candidates could not prove
+// exactness at their sparsity skip the first three kernels: every row's full
+// scores (k_score_keys; k_repair_score for float32 and labels), then k_select
+// over them.
 //   k_pilot_score   scores a strided sample of <= 2048 keys per row
 //   k_pilot_select  picks a per-row threshold from the sample (aimed at about
 //                   2.5 k candidates) and flags rows for the fallback
@@ -18,7 +22,10 @@
 //   k_select        exact top-k: over the candidates (with few rows of many
 //                   candidates, one workgroup per piece of a row), or over
 //                   the full scores for a flagged row
-//   k_attend        gathers the kept value rows, split over workgroups
+//   k_gather        softmax over the kept positions of per-head rows: gathers
+//                   their value rows (and key rows, where the selection's
+//                   scores are not the logits), split over workgroups
+//   k_attend        the same for group rows
 //   k_merge         combines the splits' (max, sum, output) partials by
 //                   log-sum-exp (only when a row is split)
 // The threshold is only a filter: the selection is exact whenever every
@@ -1173,11 +1180,11 @@ __global__ __launch_bounds__(kBlock) void k_score_keys(Params p, float *dst, int
 }
 
 // ---------------------------------------------------------------------------
-// Full scores of one (sequence b, KV head g) from labels or float32 keys:
-// part `part` of `parts` takes
-// tiles part*4 + wave, stepping by parts*4.  dst[row][j] for j < L_b; with
-// fill_tail, -inf for L_b <= j < ncap.  Every thread of the block must call
-// it (the f32 scorer stages the queries in LDS behind a barrier).
+// Full scores of one (sequence b, KV head g) from labels, float32 keys or (rows
+// that fell back) bf16 keys: part `part` of `parts` takes tiles part*4 + wave,
+// stepping by parts*4.  dst[row][j] for j < L_b; with fill_tail, -inf for L_b
+// <= j < ncap.  Every thread of the block must call it (the f32 scorer stages
+// the queries in LDS behind a barrier).
 // ---------------------------------------------------------------------------
 // Tiles in flight per wave in the pipelined full scoring: one tile's loads
 // are a single round trip (4 KB of keys, or 256 B of label rows).
@@ -1267,11 +1274,10 @@ __global__ __launch_bounds__(kBlock) void k_score_dense(Params p, float *dst, in
                                   true, q_lds);
 }
 
-// Exact fallback, scoring.  grid = (parts, B*Hkv), parts at least
-// kRepairParts (repair_parts).  A row takes the
-// fallback when every row is forced to, or when its candidates cannot prove
-// exactness: fewer than k passed, or a staging area overflowed (a per-chunk
-// count of -1).  Each workgroup derives its group's flags from the rows'
+// Exact fallback, scoring.  grid = (parts, B*Hkv) (repair_parts).  A row takes
+// the fallback when every row is forced to (here float32 keys and labels), or
+// when its candidates cannot prove exactness: fewer than k passed, or a staging
+// area overflowed (a per-chunk count of -1).  Each workgroup derives its group's flags from the rows'
 // per-chunk counts (part 0 records them in w.flags for the selection) and,
 // when a row of the group is flagged, scores its part of the group into
 // w.dense.
@@ -2626,7 +2632,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     if (MODE == 2 || (MODE == 0 && w.flags[row])) {  // the exact fallback: full scores
       if (blockIdx.y > 0) return;  // (one workgroup per row)
       if (tid == 0) atomicAdd(&w.stats[0], 1);
-      if (!w.dsel_parts)  // (else the k_dsel kernels wrote the selection)
+      if (MODE == 0 || !w.dsel_parts)  // (else the k_dsel kernels wrote the selection)
         weights_done = row_select<NT, MODE != 0>(w.dense + (int64_t)row * p.ncap + rp.lo, (uint32_t)rp.lo,
                                                   rp.hi - rp.lo, k, hist, &sh, &bs, &rsh, range,
                                                   dyn, dyn_bytes, irow, vrow, weights, p.scale);
@@ -3911,8 +3917,8 @@ hipError_t launch_select_candidates(const Params &p, const Work &w, int32_t *idx
 // about 1024 workgroups in all, up to kRepairParts per group: a launch of
 // 2048 or 4096 workgroups that only check the flags took 4.4 and 6.9 us at
 // the 128K batch-16 and the ragged paged workloads.  When every row is
-// forced onto the fallback and the groups are few, enough for about 2048 in
-// all (with one sequence each wave would otherwise score a long run of
+// forced onto the fallback (float32 keys, labels) and the groups are few,
+// enough for about 2048 in all (with one sequence each wave would otherwise score a long run of
 // tiles one after another, each waiting for its loads).
 int repair_parts(const Params &p, const Work &w) {
   const int groups = p.B * p.Hkv;
@@ -3946,12 +3952,12 @@ hipError_t launch_dense_select(const Params &p, const Work &w, int32_t *idx, hip
 }
 
 // Whether the full scoring of `parts` workgroups per (sequence, KV head)
-// takes the instance with several tiles in flight: bf16 keys or labels,
-// every wave with at least two rounds of tiles, and groups of more than one
-// row.  (With one row per group, MHA, the forced fallback of Table 2's label
-// shape at 2x took 0.377 instead of 0.338 ms at batch 1 and 1.23 instead of
-// 1.13 ms at batch 4; with groups of four rows it went from 0.257 to 0.246
-// ms at batch 1, and the 128K batch-16 key fallback from 1.10 to 1.04 ms.)
+// takes the instance with several tiles in flight: labels, or the bf16 keys of
+// groups with a row that fell back, every wave with at least two rounds of
+// tiles, and groups of more than one row.  (With one row per group, MHA, the
+// forced fallback of Table 2's label shape at 2x took 0.377 instead of 0.338
+// ms at batch 1 and 1.23 instead of 1.13 ms at batch 4; with groups of four
+// rows it went from 0.257 to 0.246 ms at batch 1.)
 static bool dense_pipelined(const Params &p, int parts) {
   const int64_t tiles = (p.ncap + kTile - 1) / kTile;
   const int64_t per_wave = (tiles + (int64_t)parts * kWaves - 1) / ((int64_t)parts * kWaves);
