@@ -1161,19 +1161,21 @@ __global__ __launch_bounds__(kBlock) void k_score_keys(Params p, float *dst, int
   // heads, with the capacity's runs on 1024 waves: 268 us, now 216).  By
   // whole factors only: just under the capacity, even runs would all be long
   // ones, one more than the chip holds (31 x 8 heads of 19523 of 19536
-  // positions: 215 -> 229 us).  Not where the tail is filled: the waves past
-  // the sequence are the ones that fill it.
+  // positions: 215 -> 229 us).  Not where much tail is filled (stand-alone
+  // scores, more than four heads to a group): the waves past the sequence are
+  // the ones that fill it.
   const int L = seq_len(p, b);
   int nkeys = blocks * kScoreBlock;
-  if (!fill && L > 0 && 2 * (int64_t)L <= p.ncap) {  // (capacities have 24 bits)
+  if ((!fill || NR <= 4) && L > 0 && 2 * (int64_t)L <= p.ncap) {  // (capacities have 24 bits)
     const uint32_t f = (uint32_t)p.ncap / (uint32_t)L;
     nkeys = (int)(((uint32_t)blocks + f - 1) / f) * kScoreBlock;
   }
   const int64_t j0 = (int64_t)run * nkeys;
   score_run<PAGED, GRP, NR>(p, dst, ld, b, g, j0, nkeys, L, sl[wv]);
-  const int64_t end = j0 + nkeys < p.ncap ? j0 + nkeys : p.ncap;
+  const int64_t f0 = (int64_t)run * blocks * kScoreBlock, f1 = f0 + blocks * kScoreBlock;
+  const int64_t end = f1 < p.ncap ? f1 : p.ncap;
   if (!fill || end <= L) return;
-  const int64_t from = j0 > L ? j0 : L;
+  const int64_t from = f0 > L ? f0 : L;
   const int64_t row0 = GRP ? (int64_t)b * p.R + g : (int64_t)b * p.R + (int64_t)g * p.G;
   for (int h = 0; h < (GRP ? 1 : p.G); ++h)
     for (int64_t j = from + lane_id(); j < end; j += 64) dst[(row0 + h) * ld + j] = -__builtin_inff();

@@ -190,8 +190,8 @@ def test_halved_waves_stay_within_the_library_workspace(sd):
 @pytest.mark.parametrize("ncap", [1040, 20000, 400000])
 def test_sequences_shorter_than_the_cache(sd, layout, Hq, Hkv, shared, ncap):
     """Calls scored in full (debug flag 1) over ragged sequences in a longer
-    cache keep what each sequence keeps in a cache of its own length (there
-    the rows are the same bit for bit, only their lists' padding differs)."""
+    cache keep what each sequence keeps in a cache of its own length, and
+    stand-alone scores are the same bit for bit, -inf past the sequence."""
     lens = [min(n, ncap) for n in (0, 1, 63, 65, 1039, 4100, 19999)]
     inp = synth.make_inputs(2, seed=6, seq_lens=lens, ncap=max(lens), Hq=Hq, Hkv=Hkv,
                             layout=layout, group_shared=shared)
@@ -209,9 +209,11 @@ def test_sequences_shorter_than_the_cache(sd, layout, Hq, Hkv, shared, ncap):
     sd.set_debug(1)
     try:
         out, idx = sd.sparse_decode_attention(q, big, sl, sp)
+        scores = sd.sparse_decode_score(q, big, sl, sp)
         for b, L in enumerate(lens):
             k_b = sd.budget(L, sp)
             assert (idx[b, :, k_b:] == -1).all()
+            assert torch.isneginf(scores[b, :, L:]).all()
             if L == 0:
                 assert (out[b] == 0).all()
                 continue
@@ -222,6 +224,8 @@ def test_sequences_shorter_than_the_cache(sd, layout, Hq, Hkv, shared, ncap):
                 own = sd.KVCache(k=cache.k[b:b + 1, :, :L].contiguous(), v=cache.v[b:b + 1, :, :L].contiguous())
             ref, ridx = sd.sparse_decode_attention(q[b:b + 1].contiguous(), own, sl[b:b + 1], sp)
             assert torch.equal(idx[b, :, :k_b], ridx[0, :, :k_b])
+            rscores = sd.sparse_decode_score(q[b:b + 1].contiguous(), own, sl[b:b + 1], sp)
+            assert torch.equal(scores[b, :, :L], rscores[0, :, :L])
             ok, worst, _ = P.out_errors(P.to_host(out[b]), P.to_host(ref[0]), "bf16")
             assert ok, worst
     finally:
