@@ -3098,8 +3098,9 @@ struct GatherAcc {
 // plain float32, were 1.1-1.4x closer to 64 bits.  (y: the sum of a batch's two
 // entries.)  bf16 outputs round at 2^-9 and are not worth the registers.
 __device__ __forceinline__ void add_exact(float &s, float &c, float y) {
-  const float t = s + y, v = t - s;
-  c += (s - (t - v)) + (y - v);
+  // (exact where s is the larger of the two; else one rounding of y is left)
+  const float t = s + y;
+  c += y - (t - s);
   s = t;
 }
 
